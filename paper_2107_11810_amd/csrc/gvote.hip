@@ -591,6 +591,22 @@ struct Parent {
   uint64_t kept_entries = 0;  // entries of all kept children
   bool unit = true;    // every multiplicity is 1
   bool fresh = false;  // its one chunk comes next, right after its pruning
+  bool lent = false;   // the count pass's arrays below belong to Run::counts
+};
+
+// What a count pass leaves behind for the pruning and the compaction of its
+// batch: the work items, pass masks, per-child counts and entries, and each
+// item's offsets in the child lists.
+struct Counts {
+  bool valid = false;
+  Item* items = nullptr;
+  uint32_t* nitems = nullptr;
+  uint64_t max_items = 0;
+  uint32_t* ioff = nullptr;
+  uint64_t* itemoff = nullptr;
+  void* masks = nullptr;
+  uint32_t* ccnt = nullptr;
+  uint32_t* cnent = nullptr;
 };
 
 struct Task {
@@ -675,6 +691,7 @@ struct Run {
   uint64_t* dooff = nullptr;
   double* m64 = nullptr;                  // POSE4DOF binary64 master, SoA stride Ntot
   void* root = nullptr;                   // root entries (grouped), owned
+  Counts counts;                          // count pass of the dive's greedy level, kept for the main search
   // search state
   std::vector<Task> stack;
   bool own_first = true;
@@ -784,17 +801,27 @@ inline unsigned gs_grid(Run& X, uint64_t n) {
 void free_parent(Run& X, Parent* pa) {
   dfree(X, pa->cells);
   if (pa->own_ents) dfree(X, pa->ents);
-  dfree(X, pa->masks);
-  dfree(X, pa->items);
-  dfree(X, pa->nitems);
   dfree(X, pa->order);
   dfree(X, pa->scount);
   dfree(X, pa->rank_of);
   dfree(X, pa->soff);
-  dfree(X, pa->cnent);
-  dfree(X, pa->ioff);
-  dfree(X, pa->itemoff);
+  if (!pa->lent) {
+    dfree(X, pa->masks);
+    dfree(X, pa->items);
+    dfree(X, pa->nitems);
+    dfree(X, pa->cnent);
+    dfree(X, pa->ioff);
+    dfree(X, pa->itemoff);
+  }
   delete pa;
+}
+
+void free_counts(Run& X) {
+  Counts& c = X.counts;
+  if (c.valid)
+    for (void* p : {(void*)c.items, (void*)c.nitems, (void*)c.ioff, (void*)c.itemoff, c.masks, (void*)c.ccnt, (void*)c.cnent})
+      dfree(X, p);
+  c = Counts{};
 }
 
 // the first n (<= 4) totals the last kernels wrote to X.dtot
@@ -1023,13 +1050,12 @@ bool want_group(const Run& X, const Batch& b) {
   return avg >= 0.5 * X.lat_bound[b.level];
 }
 
-// One expansion: incidence test and per-child counts, pruning against the
-// best key (or, for the greedy dive, keeping only the best child), then the
-// kept children sorted by count.  Returns nullptr when nothing is kept (or at
-// the last level, where the leaf keys went into the best-key reduction).
-// The batch's cells/entries are handed over to the Parent (or freed).
+// The count pass of one batch: its work items, the incidence test of every
+// (surface, child) pair, and the per-child counts (ccnt) and entries.  The
+// masked families also leave their pass masks and, above the leaves, each
+// item's survivors per child in itemcnt (scanned by the caller).
 template <int FAM, typename E, typename M>
-Parent* expand(Run& X, Batch& b, bool own_ents, bool dive) {
+void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt, uint32_t*& itemcnt) {
   const ProbC& P = X.P0;
   const int m = b.level;
   const LevelC lv = P.lev[m];
@@ -1039,15 +1065,6 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive) {
   const uint64_t nlive = std::min(b.nent, b.nlive);
   X.stats.tests += nlive * nch;
   X.stats.cells_expanded += b.ncell;
-
-  Parent* pa = new Parent();
-  pa->level = m;
-  pa->ncell = b.ncell;
-  pa->nent = b.nent;
-  pa->cells = b.cells;
-  pa->ents = b.ents;
-  pa->own_ents = own_ents;
-  pa->unit = b.unit;
 
   // work items: at most 2^ilog <= GV_ITEM entries of one cell each (the
   // count pass's surface tile, autotuned on large batches)
@@ -1076,7 +1093,6 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive) {
   // survivors child-major; linear families write one row of per-child
   // counts per item (item-major) and repeat the test in the compaction
   const bool linear = !fam_masked(FAM);
-  uint32_t* itemcnt = nullptr;
   uint32_t* itemw = nullptr;
   if (linear) {
     itemcnt = dalloc<uint32_t>(X, (uint64_t)nch * pa->max_items);
@@ -1085,7 +1101,7 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive) {
     itemcnt = dalloc<uint32_t>(X, (uint64_t)nch * pa->istride);
   }
   if (!linear) pa->masks = dalloc<M>(X, b.nent);
-  uint32_t* ccnt = dalloc<uint32_t>(X, nk);
+  ccnt = dalloc<uint32_t>(X, nk);
   pa->cnent = dalloc<uint32_t>(X, nk);
   if (!linear) {
     const uint64_t ni = itemcnt ? (uint64_t)nch * pa->istride : 0;
@@ -1184,6 +1200,51 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive) {
     dfree(X, itemw);
     itemcnt = itemw = nullptr;
   }
+}
+
+// One expansion: incidence test and per-child counts, pruning against the
+// best key (or, for the greedy dive, keeping only the best child), then the
+// kept children sorted by count.  Returns nullptr when nothing is kept (or at
+// the last level, where the leaf keys went into the best-key reduction).
+// The batch's cells/entries are handed over to the Parent (or freed).
+// lend: a greedy expansion whose count pass is kept in X.counts; when
+// X.counts is already there (the main search starting from that batch), it
+// takes the place of the count pass.
+template <int FAM, typename E, typename M>
+Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
+  const ProbC& P = X.P0;
+  const int m = b.level;
+  const LevelC lv = P.lev[m];
+  const uint32_t nch = 1u << lv.abits;
+  const bool leaf = (m + 1 == P.Lstar);
+  const uint64_t nk = (uint64_t)b.ncell * nch;
+  const bool counted = !dive && X.counts.valid;
+
+  Parent* pa = new Parent();
+  pa->level = m;
+  pa->ncell = b.ncell;
+  pa->nent = b.nent;
+  pa->cells = b.cells;
+  pa->ents = b.ents;
+  pa->own_ents = own_ents;
+  pa->unit = b.unit;
+  uint32_t* ccnt = nullptr;
+  uint32_t* itemcnt = nullptr;
+  if (counted) {
+    const Counts c = X.counts;
+    X.counts = Counts{};
+    pa->items = c.items;
+    pa->nitems = c.nitems;
+    pa->max_items = c.max_items;
+    pa->istride = (uint32_t)c.max_items;
+    pa->ioff = c.ioff;
+    pa->itemoff = c.itemoff;
+    pa->masks = c.masks;
+    pa->cnent = c.cnent;
+    ccnt = c.ccnt;
+  } else {
+    count_pass<FAM, E, M>(X, b, pa, ccnt, itemcnt);
+  }
 
   if (dive && !leaf) {
     // greedy dive: one child per cell in parent order; the kept list is
@@ -1197,7 +1258,7 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive) {
     pa->rank_of = dalloc<uint32_t>(X, nk);
     uint32_t* sn = dalloc<uint32_t>(X, nkept);
     k_pick_kept<<<nblk(nkept), 256, 0, X.st>>>(lv, nkept, ccnt, pa->cnent, pa->order, pa->scount, sn, pa->rank_of);
-    dfree(X, ccnt);
+    if (!lend) dfree(X, ccnt);
     pa->soff = dalloc<uint64_t>(X, nkept + 1);
     if (nkept <= GV_SMALL_N) {
       k_scan_small<uint32_t, uint64_t><<<1, 1024, 0, X.st>>>(sn, pa->soff, nkept, pa->soff + nkept);
@@ -1211,6 +1272,10 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive) {
       pa->itemoff = dalloc<uint64_t>(X, (uint64_t)nch * pa->istride);
       excl_scan(X, itemcnt, pa->itemoff, (uint64_t)nch * pa->istride);
       dfree(X, itemcnt);
+    }
+    if (lend) {
+      pa->lent = true;
+      X.counts = Counts{true, pa->items, pa->nitems, pa->max_items, pa->ioff, pa->itemoff, pa->masks, ccnt, pa->cnent};
     }
     HIPCHK(hipGetLastError());
     uint64_t kt[2];
@@ -1546,13 +1611,13 @@ using PackedT = std::conditional_t<fam_pose(FAM) || std::is_void_v<typename Pack
                                    typename PackOf<FAM>::T>;
 
 template <int FAM, typename E, typename M>
-Parent* expand_at(Run& X, Batch& b, bool own_ents, bool dive) {
+Parent* expand_at(Run& X, Batch& b, bool own_ents, bool dive, bool lend = false) {
   if constexpr (FAM == FAM_PLANE3D)
-    if (b.unit && b.level >= X.unit_from) return expand<FAM, EntP3u, M>(X, b, own_ents, dive);
+    if (b.unit && b.level >= X.unit_from) return expand<FAM, EntP3u, M>(X, b, own_ents, dive, lend);
   if constexpr ((FAM == FAM_POSE4DOF || FAM == FAM_POSE5DOF) && std::is_same<E, EntQ32>::value)
-    if (b.unit && b.level >= 1 && X.q24) return expand<FAM, EntQ24, M>(X, b, own_ents, dive);
-  if (b.level >= X.pack_from) return expand<FAM, PackedT<FAM, E>, M>(X, b, own_ents, dive);
-  return expand<FAM, E, M>(X, b, own_ents, dive);
+    if (b.unit && b.level >= 1 && X.q24) return expand<FAM, EntQ24, M>(X, b, own_ents, dive, lend);
+  if (b.level >= X.pack_from) return expand<FAM, PackedT<FAM, E>, M>(X, b, own_ents, dive, lend);
+  return expand<FAM, E, M>(X, b, own_ents, dive, lend);
 }
 
 template <int FAM, typename E, typename M>
@@ -1851,7 +1916,11 @@ void start_search(Run& X) {
   // instead of expanding the levels above it again.  The result cannot
   // change (the maximum leaf lies below one of these cells); measured:
   // pose4dof_1m 53 against 62 ms, eight pose problems of 1e5-1e6 matches
-  // 8-14% faster, the 256-problem set 0.77 against 0.83 s.
+  // 8-14% faster, the 256-problem set 0.77 against 0.83 s.  That batch's
+  // count pass (every child tested) is kept too (X.counts), so the main
+  // search prunes it against the dive's bound without a second one:
+  // pose4dof_1m 47.7 against 54.4 ms, 50k matches in binary64 3.7 against
+  // 4.1 ms, pose5dof_20k 3.26 against 3.50 ms.
   Batch reuse{};
   bool have_reuse = false;
   if (X.dive_cells > 0 && !X.report) {
@@ -1878,7 +1947,7 @@ void start_search(Run& X) {
         have_reuse = true;
         keep = true;
       }
-      Parent* pa = expand_at<FAM, E, M>(X, b, keep ? false : own, dv);
+      Parent* pa = expand_at<FAM, E, M>(X, b, keep ? false : own, dv, keep);
       if (!pa) break;
       uint32_t r1 = pa->nkept;
       if (!dv) {
@@ -1968,6 +2037,7 @@ bool subtree_at(Run& X, Batch& b) {
     return false;
   } else {
     if (!X.subtree || X.report || b.level < X.subtree_from || b.level + 1 >= X.P0.Lstar) return false;
+    free_counts(X);  // (the device search counts this batch itself)
     if constexpr (std::is_same<E, EntQ32>::value) {
       if (b.unit && b.level >= 1 && X.q24) {
         run_subtree<FAM, EntQ24>(X, b);
@@ -2360,6 +2430,7 @@ void epoch_release(Run& X) {
       dfree(X, t.b.ents);
     }
   }
+  free_counts(X);
   dfree(X, X.root);
   X.root = nullptr;
   dfree(X, X.m64);
