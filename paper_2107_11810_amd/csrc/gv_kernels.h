@@ -17,9 +17,10 @@ __device__ inline uint32_t wave_sum_u32(uint32_t v) {
 }
 __device__ inline uint32_t lane_id() { return threadIdx.x & 63u; }
 __device__ inline uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+// (readfirstlane returns a signed int: through uniform_u32, or a low word with
+// its top bit set would spread over the high word)
 __device__ inline uint64_t uniform_u64(uint64_t v) {
-  return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
-         (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+  return ((uint64_t)uniform_u32((uint32_t)(v >> 32)) << 32) | uniform_u32((uint32_t)v);
 }
 __device__ inline uint32_t mbcnt64(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
