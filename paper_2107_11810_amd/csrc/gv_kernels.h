@@ -138,9 +138,11 @@ __global__ void __launch_bounds__(1024) k_items_small(const Cell* __restrict__ c
 }
 
 // Prune tail of a small expansion: keepscan = exclusive prefix of keepf,
-// tot[0] = kept children, tot[1] = their entries (host-coherent memory).
+// tot[0] = kept children, tot[1] = their entries, tot[2] = the first
+// problem's best key (host-coherent memory).
 __global__ void __launch_bounds__(1024) k_keep_small(const uint32_t* __restrict__ keepf,
                                                      const uint64_t* __restrict__ keptn, uint32_t nk,
+                                                     const unsigned long long* __restrict__ best,
                                                      uint32_t* __restrict__ keepscan, uint64_t* tot) {
   __shared__ uint32_t wsum[16];
   __shared__ uint64_t wsum64[16];
@@ -166,6 +168,7 @@ __global__ void __launch_bounds__(1024) k_keep_small(const uint32_t* __restrict_
   if (threadIdx.x == 0) {
     tot[0] = kt;
     tot[1] = et;
+    tot[2] = best[0];
     __threadfence_system();
   }
 }
@@ -785,11 +788,13 @@ __global__ void k_select_kept(const uint32_t* __restrict__ keepf, const uint32_t
   }
 }
 
+// totals of a large expansion, as k_keep_small writes them
 __global__ void k_kept_total(const uint32_t* keepf, const uint32_t* keepscan, uint64_t nk, const uint64_t* esum,
-                             uint64_t* out) {
+                             const unsigned long long* best, uint64_t* out) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     out[0] = nk ? (uint64_t)keepscan[nk - 1] + keepf[nk - 1] : 0;
     out[1] = *esum;
+    out[2] = best[0];
     __threadfence_system();
   }
 }

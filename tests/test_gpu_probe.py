@@ -1,0 +1,75 @@
+"""Look-ahead pruning of pending children (csrc/gv_probe.h): with the probe
+forced on every chunk it can take (library knob GV_PROBE=2, read when a solve
+starts), off and by its rule, results equal the oracle's.  The threshold
+report is the sharpest check: a child dropped wrongly loses leaves.
+"""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2107_11810_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2107_11810_amd import gvote
+    c = gvote.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.fixture(params=["0", "1", "2"])
+def probe(request):
+    old = os.environ.get("GV_PROBE")
+    os.environ["GV_PROBE"] = request.param
+    yield request.param
+    if old is None:
+        del os.environ["GV_PROBE"]
+    else:
+        os.environ["GV_PROBE"] = old
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def OP(g, **kw):
+    return oracle.Problem(g["family"], g["cols"], g["lo"], g["hi"], g["eps"], **kw)
+
+
+# lists around the probe's blocks of 512 entries (64 lanes x 8 rows), ragged and odd sizes
+PROBLEMS = {
+    "plane3d_511": lambda: synth.plane3d(seed=511, n=511, n_in=60, sigma=0.004, eps=(0.04, 0.04, 0.04)),
+    "plane3d_513": lambda: synth.plane3d(seed=513, n=513, n_in=60, sigma=0.004, eps=(0.04, 0.04, 0.04)),
+    "plane3d_4096": lambda: synth.plane3d(seed=4096, n=4096, n_in=400, sigma=0.004, eps=(0.04, 0.04, 0.04)),
+    "plane3d_9001": lambda: synth.plane3d(seed=9001, n=9001, n_in=700, sigma=0.003, eps=(0.03, 0.03, 0.03)),
+    "plane3d_small": lambda: synth.config("plane3d_small"),
+    "plane3d_tiny": lambda: synth.config("plane3d_tiny"),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PROBLEMS))
+def test_probe_changes_nothing(ctx, probe, name):
+    g = PROBLEMS[name]()
+    _say("probe", probe, name)
+    ro = oracle.solve(OP(g))
+    r = ctx.solve(g["family"], g["cols"], g["lo"], g["hi"], g["eps"])
+    assert (r["count"], r["leaf_index"], r["sector"]) == (ro["count"], ro["leaf_index"], ro["sector"])
+    assert np.array_equal(r["inliers"], ro["inliers"])
+
+
+@pytest.mark.parametrize("name", ["plane3d_513", "plane3d_small"])
+def test_probe_loses_no_leaf(ctx, probe, name):
+    g = PROBLEMS[name]()
+    best = oracle.solve(OP(g))["count"]
+    for tau in sorted({max(1, 3 * best // 4), best, best + 1}):
+        _say("probe", probe, name, "tau", tau)
+        io, co = oracle.report(OP(g), tau)
+        ig, cg, _ = ctx.report(g["family"], g["cols"], g["lo"], g["hi"], g["eps"], tau)
+        assert np.array_equal(ig, io) and np.array_equal(cg, co)
