@@ -16,6 +16,7 @@
 // result depends on the probe.
 #pragma once
 #include "gv_kernels.h"
+#include "gv_subtree.h"
 
 // Smallest count with which a leaf of the subtree of the child (index bits
 // `pre` of level m + 1) can beat the best key: a larger count, or the same
@@ -161,4 +162,105 @@ __global__ void __launch_bounds__(256) k_probe_p3(LevelC lv, LevelC lv2, int B, 
   }
   if (lane == 0 && ntests) atomicAdd(tests, (unsigned long long)ntests);
   if (lane == 0 && nread) atomicAdd(reads, (unsigned long long)nread * sizeof(E));
+}
+
+// The popcounts of the wave's mask bits L..N-1 in lanes L..N-1
+template <int N, int L = 0> __device__ inline uint32_t bit_counts(uint32_t mask, uint32_t v = 0) {
+  if constexpr (L < N) {
+    const bool p = (mask >> L) & 1u;
+    return bit_counts<N, L + 1>(mask, put_lane<L>(v, (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(p))));
+  } else {
+    return v;
+  }
+}
+
+// Pose families, unit-weight lists, every axis splitting at the children's
+// level (lv2).  One wave takes one pending child (rank r).  It reads the
+// parent's pass masks, queues the child's survivors (their places in the
+// parent's list) in LDS, and tests them 64 at a time against the child's own
+// children, reading the entries from the parent's list; lane g < NCH counts
+// grandchild g.  The waves of a workgroup mostly hold children of one parent.
+// min_blocks as for the count kernels.
+template <int FAM, typename E> constexpr int probe_min_blocks() {
+  return FAM == FAM_POSE5DOF ? pose5_min_blocks<E>() : 4;
+}
+template <int FAM, typename E>
+__global__ void __launch_bounds__(256, (probe_min_blocks<FAM, E>())) k_probe_pose(
+    const ProbC* __restrict__ Ptab, int m, LevelC lv, LevelC lv2, int B, uint64_t idxmask,
+    const Cell* __restrict__ cells, const E* __restrict__ ents, const typename SubFam<FAM>::M* __restrict__ masks,
+    const double* __restrict__ m64, uint64_t n_root, const uint32_t* __restrict__ order,
+    const uint32_t* __restrict__ cnent, uint32_t r0, uint32_t r1, const unsigned long long* __restrict__ best,
+    uint32_t* keepc, uint64_t* csize, unsigned long long* __restrict__ tests, unsigned long long* __restrict__ reads,
+    unsigned long long* __restrict__ rechecks) {
+  using F = SubFam<FAM>;
+  constexpr int NCH = F::NCH;
+  constexpr uint64_t KIDS = NCH == 32 ? 0xffffffffull : 0xffffull;
+  __shared__ uint32_t queue[4][128];  // one wave each: at most 63 waiting and 64 new
+  const uint32_t lane = lane_id(), nch = 1u << lv.abits;
+  uint32_t* const q = queue[threadIdx.x >> 6];
+  const uint32_t wave = uniform_u32((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
+  uint64_t ntests = 0, nread = 0;
+  uint32_t nre = 0;
+  for (uint32_t r = r0 + wave; r < r1; r += nwaves) {
+    if (!uniform_u32(keepc[r - r0])) continue;
+    const uint32_t k = uniform_u32(order[r]), c = k / nch, ch = k % nch;
+    Cell C = cells[c];
+    const uint64_t off = C.off;
+    const uint32_t len = C.len, tot = uniform_u32(cnent[k]);
+    const ProbC& P = Ptab[C.prob];
+    const uint32_t need = probe_need(uniform_u64(best[C.prob]), B, idxmask, (C.prefix << lv.abits) | ch, lv.rem_next);
+    const float hope = 1.125f * (float)need / (float)max(tot, 1u);
+    const uint32_t cb = lv.cbits[ch];
+    for (int a = 0; a < GV_MAXD; a++) C.c[a] = lv.split[a] ? 2 * C.c[a] + (int32_t)((cb >> a) & 1u) : C.c[a];
+    typename F::Boxes Bx;
+    float Bf[F::NBF];
+    F::boxes(P, lv2, C, m + 1, Bx, Bf);
+    uint32_t cnt = 0, seen = 0, head = 0, tail = 0;
+    bool open = true, drop = false;
+    uint32_t mk = lane < len ? (uint32_t)masks[off + lane] : 0u;
+    for (uint32_t k0 = 0; k0 < len && open; k0 += 64) {
+      const uint32_t kn = k0 + 64 + lane;
+      const uint32_t mkn = kn < len ? (uint32_t)masks[off + kn] : 0u;  // the next row's, on its way
+      const bool p = (mk >> ch) & 1u;
+      const uint64_t bal = __builtin_amdgcn_ballot_w64(p);
+      if (p) q[(tail + mbcnt64(bal)) & 127u] = k0 + lane;
+      tail += (uint32_t)__popcll(bal);
+      mk = mkn;
+      const bool last = k0 + 64 >= len;
+      if (tail - head < 64u && !last) continue;
+      __builtin_amdgcn_wave_barrier();
+      // (the last row may leave more than 64 waiting)
+      do {
+        const uint32_t n = min(tail - head, 64u);
+        uint32_t mask = 0;
+        if (lane < n) {
+          const E e = ents[off + q[(head + lane) & 127u]];
+          mask = F::template mask_as<true, E>(P, lv2, C, m + 1, Bx, Bf, e, m64, n_root, nre);
+        }
+        head += n;
+        seen += n;
+        cnt += bit_counts<NCH>(mask);
+        if (!(__builtin_amdgcn_ballot_w64(cnt + (tot - seen) >= need) & KIDS)) {
+          drop = true;
+          open = false;
+        } else if (seen >= 512u && (__builtin_amdgcn_ballot_w64((float)cnt >= hope * (float)seen) & KIDS)) {
+          open = false;
+        }
+      } while (last && open && tail != head);
+      __builtin_amdgcn_wave_barrier();
+    }
+    ntests += (uint64_t)NCH * seen;
+    nread += seen;
+    if (drop && lane == 0) {
+      keepc[r - r0] = 0;
+      csize[r - r0] = 0;
+    }
+  }
+  if (lane == 0 && ntests) {
+    atomicAdd(tests, (unsigned long long)ntests);
+    atomicAdd(reads, (unsigned long long)nread * sizeof(E));
+  }
+  const uint32_t re = wave_sum_u32(nre);
+  if (lane == 0 && re) atomicAdd(rechecks, (unsigned long long)re);
 }

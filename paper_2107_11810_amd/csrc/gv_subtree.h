@@ -39,13 +39,18 @@ template <> struct SubFam<FAM_POSE4DOF> {
   __device__ static uint32_t mask(const ProbC& P, const LevelC& lv, const Cell& C, int m, const Boxes& B,
                                   const float* Bf, const E& e, const double* __restrict__ m64, uint64_t n_root,
                                   uint32_t& nre) {
-    if constexpr (sizeof(E) == sizeof(EntQ64)) {
-      return lv.abits == 4 ? pose_mask64<true>(P, lv, B, (int)C.sector, e.W1, e.W2, e.W3, e.xi, e.eta)
-                           : pose_mask64<false>(P, lv, B, (int)C.sector, e.W1, e.W2, e.W3, e.xi, e.eta);
-    } else {
-      return lv.abits == 4 ? pose_mask32<true>(P, lv, C, m, Bf, (int)C.sector, e, m64, n_root, nre)
-                           : pose_mask32<false>(P, lv, C, m, Bf, (int)C.sector, e, m64, n_root, nre);
-    }
+    return lv.abits == 4 ? mask_as<true, E>(P, lv, C, m, B, Bf, e, m64, n_root, nre)
+                         : mask_as<false, E>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
+  }
+  // ALL: every axis splits at this level
+  template <bool ALL, typename E>
+  __device__ static uint32_t mask_as(const ProbC& P, const LevelC& lv, const Cell& C, int m, const Boxes& B,
+                                     const float* Bf, const E& e, const double* __restrict__ m64, uint64_t n_root,
+                                     uint32_t& nre) {
+    if constexpr (sizeof(E) == sizeof(EntQ64))
+      return pose_mask64<ALL>(P, lv, B, (int)C.sector, e.W1, e.W2, e.W3, e.xi, e.eta);
+    else
+      return pose_mask32<ALL>(P, lv, C, m, Bf, (int)C.sector, e, m64, n_root, nre);
   }
 };
 template <> struct SubFam<FAM_POSE5DOF> {
@@ -60,8 +65,14 @@ template <> struct SubFam<FAM_POSE5DOF> {
   __device__ static uint32_t mask(const ProbC& P, const LevelC& lv, const Cell& C, int m, const Boxes& B,
                                   const float* Bf, const E& e, const double* __restrict__ m64, uint64_t n_root,
                                   uint32_t& nre) {
-    if (lv.abits == 5) return pose5_mask_of<true>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
-    return pose5_mask_of<false>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
+    if (lv.abits == 5) return mask_as<true, E>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
+    return mask_as<false, E>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
+  }
+  template <bool ALL, typename E>
+  __device__ static uint32_t mask_as(const ProbC& P, const LevelC& lv, const Cell& C, int m, const Boxes& B,
+                                     const float* Bf, const E& e, const double* __restrict__ m64, uint64_t n_root,
+                                     uint32_t& nre) {
+    return pose5_mask_of<ALL>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
   }
 };
 

@@ -1479,16 +1479,46 @@ void plan_chunks(Run& X, Parent* pa, std::vector<std::pair<uint32_t, uint32_t>>&
 // bound.  A grandchild's list is estimated as the kept children's mean length
 // shrunk once more by the ratio this level showed (kept children's mean over
 // the parents' mean).  plane3d_1m: 319 against 693 ms and 255 against 542 ms
-// (two inputs), 61k points 4.8 against 6.8 ms.  Under kProbeMin entries the
-// launch and the wait for the totals cost what the lists would.
+// (two inputs), 61k points 4.8 against 6.8 ms; pose4dof_1m 30.8 against
+// 44.2 ms (children of 6.9k entries).  Lists of a few rows end before a wave
+// can stop early, and their set-up then costs more than the lists: probed,
+// pose5dof_20k (children of 300 entries) took 3.54 against 3.24 ms and 64
+// served problems (10 to 400) 841 against 294 ms.  Under kProbeMin entries in
+// all, the launch and the wait for the totals cost what the lists would.
 constexpr uint64_t kProbeMin = 2ull << 20;
+constexpr double kProbeLen = 1024.0;  // mean entries of a child
 bool want_probe(const Run& X, const Parent* pa) {
   if (!X.probe || !pa->unit || X.probs.size() != 1 || !pa->nlive) return false;
   if (X.probe == 2) return true;
   if (pa->kept_entries < kProbeMin) return false;
   const double child = (double)pa->kept_entries / (double)pa->nkept;
   const double ratio = child / ((double)pa->nlive / (double)pa->ncell);
-  return ratio * child < (double)(pa->best >> X.P0.B);
+  return child >= kProbeLen && ratio * child < (double)(pa->best >> X.P0.B);
+}
+
+// families, entries and levels the probe kernels take: every axis splits at
+// the parent's level (linear) and at the children's
+template <int FAM, typename E> constexpr bool probe_family() {
+  return FAM == FAM_PLANE3D ? sizeof(E) <= 8 : fam_pose(FAM) && !std::is_same<E, EntQ32>::value;
+}
+template <int FAM, typename E> bool probe_fits(const ProbC& P, int level) {
+  if (!probe_family<FAM, E>() || level + 1 >= P.Lstar) return false;
+  return P.lev[level + 1].abits == P.d && (fam_pose(FAM) || P.lev[level].abits == P.d);
+}
+
+template <int FAM, typename E, typename M>
+void probe_chunk(Run& X, Parent* pa, uint32_t r0, uint32_t r1, uint32_t* keepc, uint64_t* csize) {
+  const ProbC& P = X.P0;
+  const LevelC &lv = P.lev[pa->level], &lv2 = P.lev[pa->level + 1];
+  if constexpr (FAM == FAM_PLANE3D && probe_family<FAM, E>()) {
+    k_probe_p3<E><<<nblk(pa->ncell, 4), 256, 0, X.st>>>(lv, lv2, P.B, P.idxmask, pa->cells, pa->ncell,
+                                                        (const E*)pa->ents, pa->rank_of, pa->cnent, r0, r1, X.dbest,
+                                                        keepc, csize, X.dtests, X.dtests + 1);
+  } else if constexpr (probe_family<FAM, E>()) {
+    k_probe_pose<FAM, E><<<nblk(r1 - r0, 4), 256, 0, X.st>>>(
+        X.dP, pa->level, lv, lv2, P.B, P.idxmask, pa->cells, (const E*)pa->ents, (const M*)pa->masks, X.m64, X.Ntot,
+        pa->order, pa->cnent, r0, r1, X.dbest, keepc, csize, X.dtests, X.dtests + 1, X.drecheck);
+  }
 }
 
 // Materialize one chunk [r0, r1) of a parent as a new batch (after cutting it
@@ -1511,17 +1541,13 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
   pa->fresh = false;
   k_chunk_keep<<<nblk(nr), 256, 0, X.st>>>(pa->order, pa->scount, pa->cells, nch, X.dbest, P.B, r0, r1, pa->cnent,
                                             keepc, csize, fresh ? 1 : 0);
-  if constexpr (FAM == FAM_PLANE3D && sizeof(E) <= 8) {
-    if (lv.abits == 3 && pa->level + 1 < P.Lstar && P.lev[pa->level + 1].abits == 3 && want_probe(X, pa)) {
-      fresh = false;
-      auto evp = ev_begin(X, 0);
-      X.stats.test_launches++;
-      k_probe_p3<E><<<nblk(pa->ncell, 4), 256, 0, X.st>>>(lv, P.lev[pa->level + 1], P.B, P.idxmask, pa->cells,
-                                                          pa->ncell, (const E*)pa->ents, pa->rank_of, pa->cnent, r0,
-                                                          r1, X.dbest, keepc, csize, X.dtests, X.dtests + 1);
-      ev_end(X, evp);
-      HIPCHK(hipGetLastError());
-    }
+  if (probe_fits<FAM, E>(P, pa->level) && want_probe(X, pa)) {
+    fresh = false;
+    auto evp = ev_begin(X, 0);
+    X.stats.test_launches++;
+    probe_chunk<FAM, E, M>(X, pa, r0, r1, keepc, csize);
+    ev_end(X, evp);
+    HIPCHK(hipGetLastError());
   }
   if (nr <= GV_SMALL_N) {
     k_chunk_small<<<1, 1024, 0, X.st>>>(keepc, csize, nr, cidx, coff, X.dtot);

@@ -51,6 +51,13 @@ PROBLEMS = {
     "plane3d_9001": lambda: synth.plane3d(seed=9001, n=9001, n_in=700, sigma=0.003, eps=(0.03, 0.03, 0.03)),
     "plane3d_small": lambda: synth.config("plane3d_small"),
     "plane3d_tiny": lambda: synth.config("plane3d_tiny"),
+    "pose4dof_tiny": lambda: synth.config("pose4dof_tiny"),
+    "pose4dof_small": lambda: synth.config("pose4dof_small"),
+    "pose4dof_flat": lambda: synth.config("pose4dof_small_flat"),
+    "pose4dof_5003": lambda: synth.pose4dof(seed=5003, n=5003, n_in=300, noise_deg=0.2, eps_m=4.0, eps_deg=2.0,
+                                            rho_max=80.0),
+    "pose5dof_tiny": lambda: synth.config("pose5dof_tiny"),
+    "pose5dof_small": lambda: synth.config("pose5dof_small"),
 }
 
 
@@ -59,12 +66,13 @@ def test_probe_changes_nothing(ctx, probe, name):
     g = PROBLEMS[name]()
     _say("probe", probe, name)
     ro = oracle.solve(OP(g))
-    r = ctx.solve(g["family"], g["cols"], g["lo"], g["hi"], g["eps"])
-    assert (r["count"], r["leaf_index"], r["sector"]) == (ro["count"], ro["leaf_index"], ro["sector"])
-    assert np.array_equal(r["inliers"], ro["inliers"])
+    for precision in (0, 1):
+        r = ctx.solve(g["family"], g["cols"], g["lo"], g["hi"], g["eps"], precision=precision)
+        assert (r["count"], r["leaf_index"], r["sector"]) == (ro["count"], ro["leaf_index"], ro["sector"])
+        assert np.array_equal(r["inliers"], ro["inliers"])
 
 
-@pytest.mark.parametrize("name", ["plane3d_513", "plane3d_small"])
+@pytest.mark.parametrize("name", ["plane3d_513", "plane3d_small", "pose4dof_small", "pose5dof_tiny"])
 def test_probe_loses_no_leaf(ctx, probe, name):
     g = PROBLEMS[name]()
     best = oracle.solve(OP(g))["count"]
