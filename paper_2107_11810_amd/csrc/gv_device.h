@@ -125,12 +125,17 @@ template <> struct EntOf<FAM_SIM2D> { using T = EntS2; };
 //   LINE2D : int16 K, int16 F, u32 w
 //   PLANE3D: lo = K1 (13 bits, signed) | K2 (13, signed) | w bits 0..5,
 //            hi = F (16, signed) | w bits 6..21
-// RAY3D keeps its full entry.
+// and half the full entry for the families with two dependent axes:
+//   RAY3D  : int16 K1, K2, F1, F2, u32 w (30 bits) | tag << 30 (12 bytes)
+//   SIM2D  : int16 K00, K01, K10, K11, F0, F1, u32 w (16 bytes)
 #define GV_P3_KMAX 4095    // |K| limit of a packed PLANE3D entry
 #define GV_P3_FMAX 32767   // |F| limit
 #define GV_P3_WMAX 4194303 // weight limit (22 bits)
-#define GV_L2_MAX 32767    // |K|, |F| limit of a packed LINE2D entry
+#define GV_L2_MAX 32767    // |K|, |F| limit of a packed LINE2D, RAY3D or SIM2D entry
+#define GV_R3_WMAX 1073741823  // weight limit of a packed RAY3D entry (30 bits)
 struct __attribute__((aligned(8))) EntL2p { int16_t K, F; uint32_t w; };
+struct __attribute__((aligned(4))) EntR3p { int16_t K1, K2, F1, F2; uint32_t wt; };
+struct __attribute__((aligned(16))) EntS2p { int16_t K00, K01, K10, K11, F0, F1; uint32_t w; };
 struct __attribute__((aligned(8))) EntP3p { uint32_t lo, hi; };
 // PLANE3D unit-weight lists at the deep levels, where the slopes fit 8 bits:
 // one word, K1 (8, signed) | K2 (8, signed) << 8 | F (16, signed) << 16, and
@@ -140,6 +145,8 @@ struct __attribute__((aligned(4))) EntP3u { uint32_t v; };
 template <int FAM> struct PackOf { using T = void; };  // no packed entry
 template <> struct PackOf<FAM_LINE2D> { using T = EntL2p; };
 template <> struct PackOf<FAM_PLANE3D> { using T = EntP3p; };
+template <> struct PackOf<FAM_RAY3D> { using T = EntR3p; };
+template <> struct PackOf<FAM_SIM2D> { using T = EntS2p; };
 
 __device__ __host__ inline int32_t sext_field(uint32_t x, int pos, int bits) {
   return (int32_t)(x << (32 - pos - bits)) >> (32 - bits);
@@ -151,11 +158,9 @@ __device__ __host__ inline EntP3p pack_p3(int32_t K1, int32_t K2, int32_t F, uin
   return e;
 }
 
-// round-half-to-even of x/2 for an integer x
-__device__ __host__ inline int32_t rne_half(int32_t x) {
-  int32_t q = x >> 1;  // floor(x/2)
-  return (x & 1) ? (q + (q & 1)) : q;
-}
+// round-half-to-even of x/2 for an integer x: an odd x goes up exactly where
+// floor(x/2), bit 1 of x, is odd (an even x loses the added 1 in the shift)
+__device__ __host__ inline int32_t rne_half(int32_t x) { return (x + ((x >> 1) & 1)) >> 1; }
 
 __device__ inline int32_t imin32(int32_t a, int32_t b) { return a < b ? a : b; }
 __device__ inline int32_t imax32(int32_t a, int32_t b) { return a < b ? b : a; }
@@ -304,6 +309,20 @@ template <int FAM> __device__ __host__ inline LinS load_ent(const EntP3u& e) {
   return s;
 }
 
+template <int FAM> __device__ __host__ inline LinS load_ent(const EntR3p& e) {
+  LinS s = lin_zero<FAM>();
+  s.K[0][0] = e.K1; s.K[1][0] = e.K2; s.F[0] = e.F1; s.F[1] = e.F2;
+  s.w = (int32_t)(e.wt & GV_R3_WMAX);
+  s.tag = (int32_t)(e.wt >> 30);
+  return s;
+}
+template <int FAM> __device__ __host__ inline LinS load_ent(const EntS2p& e) {
+  LinS s = lin_zero<FAM>();
+  s.K[0][0] = e.K00; s.K[0][1] = e.K01; s.K[1][0] = e.K10; s.K[1][1] = e.K11;
+  s.F[0] = e.F0; s.F[1] = e.F1; s.w = (int32_t)e.w;
+  return s;
+}
+
 // register state -> entry; a packed store clears ok when a value does not fit
 template <int FAM, typename E> __device__ __host__ inline E store_ent(const LinS& s, bool& ok);
 template <> __device__ __host__ inline EntL2 store_ent<FAM_LINE2D, EntL2>(const LinS& s, bool&) {
@@ -337,6 +356,23 @@ template <> __device__ __host__ inline EntP3p store_ent<FAM_PLANE3D, EntP3p>(con
   ok = ok && abs(s.K[0][0]) <= GV_P3_KMAX && abs(s.K[0][1]) <= GV_P3_KMAX && abs(s.F[0]) <= GV_P3_FMAX &&
        (uint32_t)s.w <= GV_P3_WMAX;
   return pack_p3(s.K[0][0], s.K[0][1], s.F[0], (uint32_t)s.w);
+}
+
+template <> __device__ __host__ inline EntR3p store_ent<FAM_RAY3D, EntR3p>(const LinS& s, bool& ok) {
+  ok = ok && abs(s.K[0][0]) <= GV_L2_MAX && abs(s.K[1][0]) <= GV_L2_MAX && abs(s.F[0]) <= GV_L2_MAX &&
+       abs(s.F[1]) <= GV_L2_MAX && (uint32_t)s.w <= GV_R3_WMAX;
+  EntR3p e;
+  e.K1 = (int16_t)s.K[0][0]; e.K2 = (int16_t)s.K[1][0]; e.F1 = (int16_t)s.F[0]; e.F2 = (int16_t)s.F[1];
+  e.wt = (uint32_t)s.w | ((uint32_t)s.tag << 30);
+  return e;
+}
+template <> __device__ __host__ inline EntS2p store_ent<FAM_SIM2D, EntS2p>(const LinS& s, bool& ok) {
+  ok = ok && abs(s.K[0][0]) <= GV_L2_MAX && abs(s.K[0][1]) <= GV_L2_MAX && abs(s.K[1][0]) <= GV_L2_MAX &&
+       abs(s.K[1][1]) <= GV_L2_MAX && abs(s.F[0]) <= GV_L2_MAX && abs(s.F[1]) <= GV_L2_MAX;
+  EntS2p e;
+  e.K00 = (int16_t)s.K[0][0]; e.K01 = (int16_t)s.K[0][1]; e.K10 = (int16_t)s.K[1][0]; e.K11 = (int16_t)s.K[1][1];
+  e.F0 = (int16_t)s.F[0]; e.F1 = (int16_t)s.F[1]; e.w = (uint32_t)s.w;
+  return e;
 }
 
 template <> __device__ __host__ inline EntP3u store_ent<FAM_PLANE3D, EntP3u>(const LinS& s, bool& ok) {
@@ -386,10 +422,20 @@ template <int FAM> __device__ inline bool lin_meets(const LinS& s, const LevelC&
   return ok;
 }
 
+// axes of a linear family, and the child bits (axis j's in bit j) of digit ch
+// where every axis splits: the digit holds them in axis order, most
+// significant first
+template <int FAM> __device__ inline constexpr int lin_axes() { return FAM == FAM_LINE2D ? 2 : (FAM == FAM_SIM2D ? 4 : 3); }
+template <int FAM> __device__ inline constexpr uint32_t all_bits(uint32_t ch) {
+  uint32_t cb = 0;
+  for (int j = 0; j < lin_axes<FAM>(); j++) cb |= ((ch >> (lin_axes<FAM>() - 1 - j)) & 1u) << j;
+  return cb;
+}
+
 // Canonization of the surface at the child cell (Sec. 3.2.1): translate to
 // the child's min corner, round essential and free parameters to the
-// child's lattice (half to even).
-template <int FAM> __device__ inline LinS lin_canon_child(const LinS& s, const LevelC& lv, uint32_t cb) {
+// child's lattice (half to even).  ALL: every axis splits at this level.
+template <int FAM, bool ALL = false> __device__ inline LinS lin_canon_child(const LinS& s, const LevelC& lv, uint32_t cb) {
   LinS o = s;
 #pragma unroll
   for (int qi = 0; qi < nQ<FAM>(); qi++) {
@@ -398,12 +444,12 @@ template <int FAM> __device__ inline LinS lin_canon_child(const LinS& s, const L
 #pragma unroll
     for (int pi = 0; pi < nP<FAM>(); pi++) {
       int j = Pax<FAM>(s, pi);
-      int32_t sp = sel4(lv.split, j);
+      int32_t sp = ALL ? 1 : sel4(lv.split, j);
       int32_t b = (int32_t)((cb >> j) & 1u);
       if (sp) v += s.K[qi][pi] * b;
       o.K[qi][pi] = sp ? rne_half(s.K[qi][pi]) : s.K[qi][pi];
     }
-    int32_t spq = sel4(lv.split, q);
+    int32_t spq = ALL ? 1 : sel4(lv.split, q);
     int32_t bq = (int32_t)((cb >> q) & 1u);
     if (spq) v -= bq * sel4(lv.H, q);
     o.F[qi] = rne_half(v);

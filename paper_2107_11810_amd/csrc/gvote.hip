@@ -2201,21 +2201,29 @@ void build_linear(Run& X) {
   }
   // first level from which every list value fits the packed entry: slopes
   // as above, heights within the cell plus its pads plus the slope spans
+  // (RAY3D: any axis can be the parameter, so the slowest-halving one)
   uint64_t nmax = 0;
   for (ProbRec* pr : X.probs) nmax = std::max<uint64_t>(nmax, (uint64_t)pr->n);
   X.pack_from = 1 << 30;
-  if (X.ctx->pack && (FAM == FAM_LINE2D || (FAM == FAM_PLANE3D && nmax <= GV_P3_WMAX))) {
-    const int q = (FAM == FAM_LINE2D) ? 1 : 2;
-    const double kmax = (FAM == FAM_LINE2D) ? GV_L2_MAX : GV_P3_KMAX;
-    const double fmax = (FAM == FAM_LINE2D) ? GV_L2_MAX : GV_P3_FMAX;
+  const uint64_t wmax = FAM == FAM_PLANE3D ? GV_P3_WMAX : (FAM == FAM_RAY3D ? GV_R3_WMAX : ~0ull);
+  if (X.ctx->pack && nmax <= wmax) {
+    const int q0 = FAM == FAM_LINE2D ? 1 : (FAM == FAM_RAY3D ? 0 : 2);  // first dependent axis
+    const int d = X.probs[0]->S.d;
+    const double kmax = (FAM == FAM_PLANE3D) ? GV_P3_KMAX : GV_L2_MAX;
+    const double fmax = (FAM == FAM_PLANE3D) ? GV_P3_FMAX : GV_L2_MAX;
     for (int m = P.Lstar - 1; m >= 1; m--) {
       double kb = 0.0, ks = 0.0;
-      for (int pi = 0; pi < ((FAM == FAM_PLANE3D) ? 2 : 1); pi++) {
-        const double km = std::ceil((double)mk_all / std::ldexp(1.0, std::min(m, P.L[pi]))) + 1.0;
+      for (int pi = 0; pi < ((FAM == FAM_PLANE3D || FAM == FAM_SIM2D) ? 2 : 1); pi++) {
+        int h = std::min(m, P.L[pi]);
+        if (FAM == FAM_RAY3D)
+          for (int j = 0; j < d; j++) h = std::min(h, P.L[j]);
+        const double km = std::ceil((double)mk_all / std::ldexp(1.0, h)) + 1.0;
         kb = std::max(kb, km);
         ks += km;
       }
-      const double fb = (double)P.lev[m].H[q] + (double)P.lev[m - 1].padu[q] + 2.0 * ks + 4.0;
+      double fb = 0.0;
+      for (int q = q0; q < d; q++)
+        fb = std::max(fb, (double)P.lev[m].H[q] + (double)P.lev[m - 1].padu[q] + 2.0 * ks + 4.0);
       if (kb > kmax || fb > fmax) break;
       X.pack_from = m;
     }
