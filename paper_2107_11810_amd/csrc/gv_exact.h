@@ -87,16 +87,14 @@ __global__ void k_root_x(const ProbC* __restrict__ Pp, Cols cols, int64_t n, Ent
 }
 
 // Count pass: one wave per item; per entry the pass mask over the cell's
-// children (stored for the compaction), per child the summed multiplicities
-// (one atomic per item and child) and the item's survivors (for the
-// compaction's write offsets).
+// children (stored for the compaction), and the item's row of survivors and
+// weights per child.
 template <int BF, bool UNIT, typename M>
 __global__ void __launch_bounds__(256) k_count_x(const ProbC* __restrict__ Ptab, int m, LevelC lv,
                                                  const Cell* __restrict__ cells, const Item* __restrict__ items,
                                                  const uint32_t* __restrict__ nitems_p, const EntX* __restrict__ ents,
-                                                 M* __restrict__ masks, uint32_t* __restrict__ ccnt,
-                                                 uint32_t* __restrict__ cnent, uint32_t* __restrict__ itemcnt,
-                                                 uint32_t istride) {
+                                                 M* __restrict__ masks, uint32_t* __restrict__ icnt,
+                                                 uint32_t* __restrict__ iw) {
   constexpr int NC = 8 * (int)sizeof(M);  // children a mask holds (8, or 16 for four split axes)
   const uint32_t nch = 1u << lv.abits;
   const uint32_t lane = lane_id();
@@ -134,18 +132,7 @@ __global__ void __launch_bounds__(256) k_count_x(const ProbC* __restrict__ Ptab,
         }
       }
     }
-#pragma unroll
-    for (int ch = 0; ch < NC; ch++) {
-      if ((uint32_t)ch < nch) {
-        const uint32_t n = UNIT ? an[ch] : wave_sum_u32(an[ch]);
-        const uint32_t w = UNIT ? n : wave_sum_u32(aw[ch]);
-        if (lane == 0 && n) {
-          atomicAdd(&ccnt[I.cell * nch + ch], w);
-          atomicAdd(&cnent[I.cell * nch + ch], n);
-          if (istride) itemcnt[(uint64_t)ch * istride + it] = n;
-        }
-      }
-    }
+    put_row<NC, UNIT>(an, aw, nch, it, icnt, iw);
   }
 }
 

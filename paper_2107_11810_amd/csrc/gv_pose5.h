@@ -327,10 +327,9 @@ __global__ void __launch_bounds__(256, pose5_min_blocks<E>()) k_count_pose5(cons
                                                      const Cell* __restrict__ cells, const Item* __restrict__ items,
                                                      const uint32_t* __restrict__ nitems_p, const E* __restrict__ ents,
                                                      const double* __restrict__ m64, uint64_t n_root,
-                                                     uint32_t* __restrict__ masks, uint32_t* __restrict__ ccnt,
-                                                     uint32_t* __restrict__ cnent,
-                                                     unsigned long long* __restrict__ rechecks,
-                                                     uint32_t* __restrict__ itemcnt, uint32_t istride) {
+                                                     uint32_t* __restrict__ masks, uint32_t* __restrict__ icnt,
+                                                     uint32_t* __restrict__ iw,
+                                                     unsigned long long* __restrict__ rechecks) {
   constexpr bool F64 = std::is_same<E, EntQ64>::value;
   const uint32_t nch = ALL ? 32u : 1u << lv.abits;
   const uint32_t lane = lane_id();
@@ -362,6 +361,7 @@ __global__ void __launch_bounds__(256, pose5_min_blocks<E>()) k_count_pose5(cons
 #pragma unroll
         for (int g = 0; g < 8; g++) pk[g] += (((mask >> (4 * g)) & 0xFu) * 0x204081u) & 0x01010101u;
       }
+      uint32_t vn = 0;  // lane ch: child ch's entries
 #pragma unroll
       for (int g = 0; g < 8; g++) {
         if ((uint32_t)(4 * g) >= nch) break;
@@ -369,15 +369,9 @@ __global__ void __launch_bounds__(256, pose5_min_blocks<E>()) k_count_pose5(cons
         const uint32_t od = wave_sum_u32((pk[g] >> 8) & 0x00FF00FFu);  // children 4g + 1, 4g + 3
         const uint32_t n4[4] = {ev & 0xFFFFu, od & 0xFFFFu, ev >> 16, od >> 16};
 #pragma unroll
-        for (int b = 0; b < 4; b++) {
-          const uint32_t ch = 4 * g + b, n = n4[b];
-          if (lane == 0 && ch < nch && n) {
-            atomicAdd(&ccnt[I.cell * nch + ch], n);
-            atomicAdd(&cnent[I.cell * nch + ch], n);
-            if (istride) itemcnt[(uint64_t)ch * istride + it] = n;
-          }
-        }
+        for (int b = 0; b < 4; b++) vn = lane == (uint32_t)(4 * g + b) ? n4[b] : vn;
       }
+      if (lane < nch) icnt[(uint64_t)it * nch + lane] = vn;
     } else {
       uint32_t aw[32], an[32];
 #pragma unroll
@@ -399,18 +393,7 @@ __global__ void __launch_bounds__(256, pose5_min_blocks<E>()) k_count_pose5(cons
           an[ch] += p ? 1u : 0u;
         }
       }
-#pragma unroll
-      for (int ch = 0; ch < 32; ch++) {
-        if ((uint32_t)ch < nch) {
-          const uint32_t n = wave_sum_u32(an[ch]);
-          const uint32_t w = wave_sum_u32(aw[ch]);
-          if (lane == 0 && n) {
-            atomicAdd(&ccnt[I.cell * nch + ch], w);
-            atomicAdd(&cnent[I.cell * nch + ch], n);
-            if (istride) itemcnt[(uint64_t)ch * istride + it] = n;
-          }
-        }
-      }
+      put_row<32, false>(an, aw, nch, it, icnt, iw);
     }
   }
   if constexpr (!F64) {

@@ -586,8 +586,7 @@ struct Parent {
   uint64_t* soff = nullptr;     // rank -> first entry (nkept + 1 values)
   uint32_t* cnent = nullptr;    // child -> entries
   uint32_t* ioff = nullptr;     // cell -> its first item
-  uint64_t* itemoff = nullptr;  // child-major exclusive scan of per-item survivors
-  uint32_t istride = 0;
+  uint64_t* itemoff = nullptr;  // (item, child) -> the item's offset inside the child's list
   int pending = 0;
   bool sorted = true;  // children in descending count order
   uint64_t kept_entries = 0;  // entries of all kept children
@@ -640,7 +639,6 @@ struct Run {
   unsigned long long* dbest = nullptr;    // [nprob]
   unsigned long long* drecheck = nullptr;
   uint64_t* dtot = nullptr;
-  uint32_t* dummy = nullptr;              // sink for outputs a leaf-level pass does not need
   unsigned long long* dreads = nullptr;   // parent bytes read by compaction passes
   int* dovf = nullptr;                    // set when a packed entry could not hold a value
   int pack_from = 1 << 30;                // lists of this level and deeper use the packed entry
@@ -1055,11 +1053,11 @@ bool want_group(const Run& X, const Batch& b) {
 }
 
 // The count pass of one batch: its work items, the incidence test of every
-// (surface, child) pair, and the per-child counts (ccnt) and entries.  The
-// masked families also leave their pass masks and, above the leaves, each
-// item's survivors per child in itemcnt (scanned by the caller).
+// (surface, child) pair, and the per-child counts (ccnt) and entries and each
+// item's offsets in the child lists.  The masked families also leave their
+// pass masks.
 template <int FAM, typename E, typename M>
-void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt, uint32_t*& itemcnt) {
+void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
   const ProbC& P = X.P0;
   const int m = b.level;
   const LevelC lv = P.lev[m];
@@ -1092,25 +1090,15 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt, uint32_t*& itemcn
     k_item_fill<<<nblk(b.ncell), 256, 0, X.st>>>(b.cells, b.ncell, ilog, nitem, pa->ioff, pa->items, pa->nitems);
   }
   dfree(X, nitem);
-  pa->istride = (uint32_t)pa->max_items;
-  // POSE4DOF keeps per-entry pass masks and counts with atomics, per-item
-  // survivors child-major; linear families write one row of per-child
-  // counts per item (item-major) and repeat the test in the compaction
+  // one row of per-child entries (and weights) per item; the masked families
+  // store per-entry pass masks, the linear ones repeat the test in the
+  // compaction
   const bool linear = !fam_masked(FAM);
-  uint32_t* itemw = nullptr;
-  if (linear) {
-    itemcnt = dalloc<uint32_t>(X, (uint64_t)nch * pa->max_items);
-    if (!b.unit) itemw = dalloc<uint32_t>(X, (uint64_t)nch * pa->max_items);
-  } else if (!leaf) {
-    itemcnt = dalloc<uint32_t>(X, (uint64_t)nch * pa->istride);
-  }
+  uint32_t* itemcnt = dalloc<uint32_t>(X, (uint64_t)nch * pa->max_items);
+  uint32_t* itemw = b.unit ? nullptr : dalloc<uint32_t>(X, (uint64_t)nch * pa->max_items);
   if (!linear) pa->masks = dalloc<M>(X, b.nent);
   ccnt = dalloc<uint32_t>(X, nk);
   pa->cnent = dalloc<uint32_t>(X, nk);
-  if (!linear) {
-    const uint64_t ni = itemcnt ? (uint64_t)nch * pa->istride : 0;
-    k_zero3<<<gs_grid(X, std::max(nk, ni)), 256, 0, X.st>>>(ccnt, nk, pa->cnent, nk, itemcnt, ni);
-  }
   int cand;
   const int gpc = grid_pick(X, 0, tbytes, &cand);
   const unsigned grid = (unsigned)std::min<uint64_t>((pa->max_items + 3) / 4, (uint64_t)X.ctx->n_cu * gpc);
@@ -1120,8 +1108,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt, uint32_t*& itemcn
   if constexpr (FAM == FAM_POSE5DOF) {
 #define GV_COUNT_POSE5(U, A)                                                                                     \
   k_count_pose5<E, U, A><<<grid, 256, 0, X.st>>>(X.dP, m, lv, b.cells, pa->items, pa->nitems, (const E*)b.ents,   \
-                                                X.m64, X.Ntot, (uint32_t*)pa->masks, ccnt, pa->cnent, X.drecheck, \
-                                                itemcnt ? itemcnt : X.dummy, itemcnt ? pa->istride : 0u)
+                                                X.m64, X.Ntot, (uint32_t*)pa->masks, itemcnt, itemw, X.drecheck)
     static_assert(std::is_same<M, uint32_t>::value, "5-DoF masks are 32-bit");
     const bool all = lv.abits == 5;
     if (b.unit) {
@@ -1135,8 +1122,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt, uint32_t*& itemcn
   } else if constexpr (FAM == FAM_POSE4DOF) {
 #define GV_COUNT_POSE(U, A)                                                                                 \
   k_count_pose<E, U, A><<<grid, 256, 0, X.st>>>(X.dP, m, lv, b.cells, pa->items, pa->nitems, (const E*)b.ents, \
-                                                X.m64, X.Ntot, (uint16_t*)pa->masks, ccnt, pa->cnent, X.drecheck, \
-                                                itemcnt ? itemcnt : X.dummy, itemcnt ? pa->istride : 0u)
+                                                X.m64, X.Ntot, (uint16_t*)pa->masks, itemcnt, itemw, X.drecheck)
     // every axis splits at most levels: that variant has no per-axis checks
     const bool all = lv.abits == 4;
     if (b.unit) {
@@ -1150,13 +1136,10 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt, uint32_t*& itemcn
   } else if constexpr (fam_exact(FAM)) {
     if (b.unit)
       k_count_x<fam_base(FAM), true, M><<<grid, 256, 0, X.st>>>(X.dP, m, lv, b.cells, pa->items, pa->nitems,
-                                                            (const EntX*)b.ents, (M*)pa->masks, ccnt, pa->cnent,
-                                                            itemcnt ? itemcnt : X.dummy, itemcnt ? pa->istride : 0u);
+                                                            (const EntX*)b.ents, (M*)pa->masks, itemcnt, itemw);
     else
       k_count_x<fam_base(FAM), false, M><<<grid, 256, 0, X.st>>>(X.dP, m, lv, b.cells, pa->items, pa->nitems,
-                                                             (const EntX*)b.ents, (M*)pa->masks, ccnt,
-                                                             pa->cnent, itemcnt ? itemcnt : X.dummy,
-                                                             itemcnt ? pa->istride : 0u);
+                                                             (const EntX*)b.ents, (M*)pa->masks, itemcnt, itemw);
   } else {
 #define GV_COUNT_LIN(U, N) \
   k_count_lin<FAM, U, E, N><<<grid, 256, 0, X.st>>>(lv, pa->items, pa->nitems, (const E*)b.ents, itemcnt, itemw)
@@ -1181,29 +1164,28 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt, uint32_t*& itemcn
   }
   ev_end(X, evp);
   HIPCHK(hipGetLastError());
-  if constexpr (!fam_masked(FAM)) {
-    // per-cell counts and per-item offsets from the items' rows
-    if (!leaf) pa->itemoff = dalloc<uint64_t>(X, (uint64_t)nch * pa->max_items);
+  // per-cell counts and per-item offsets from the items' rows
+  if (!leaf) pa->itemoff = dalloc<uint64_t>(X, (uint64_t)nch * pa->max_items);
 #define GV_CELL_SCAN(U, N)                                                                                      \
-  k_cell_scan<N, U><<<nblk((uint64_t)b.ncell * N), 256, 0, X.st>>>(b.cells, b.ncell, ilog, pa->ioff, itemcnt, itemw, \
-                                                                   pa->itemoff, ccnt, pa->cnent)
-    switch ((b.unit ? 32 : 0) | nch) {
-      case 32 | 2: GV_CELL_SCAN(true, 2); break;
-      case 32 | 4: GV_CELL_SCAN(true, 4); break;
-      case 32 | 8: GV_CELL_SCAN(true, 8); break;
-      case 32 | 16: GV_CELL_SCAN(true, 16); break;
-      case 2: GV_CELL_SCAN(false, 2); break;
-      case 4: GV_CELL_SCAN(false, 4); break;
-      case 8: GV_CELL_SCAN(false, 8); break;
-      case 16: GV_CELL_SCAN(false, 16); break;
-      default: throw DevErr{GV_EINVAL};
-    }
-#undef GV_CELL_SCAN
-    HIPCHK(hipGetLastError());
-    dfree(X, itemcnt);
-    dfree(X, itemw);
-    itemcnt = itemw = nullptr;
+  k_cell_scan<N, U><<<nblk((uint64_t)b.ncell * N), 256, 0, X.st>>>(b.cells, b.ncell, ilog, pa->ioff, itemcnt, \
+                                                                   itemw, pa->itemoff, ccnt, pa->cnent)
+  switch ((b.unit ? 64 : 0) | nch) {
+    case 64 | 2: GV_CELL_SCAN(true, 2); break;
+    case 64 | 4: GV_CELL_SCAN(true, 4); break;
+    case 64 | 8: GV_CELL_SCAN(true, 8); break;
+    case 64 | 16: GV_CELL_SCAN(true, 16); break;
+    case 64 | 32: GV_CELL_SCAN(true, 32); break;
+    case 2: GV_CELL_SCAN(false, 2); break;
+    case 4: GV_CELL_SCAN(false, 4); break;
+    case 8: GV_CELL_SCAN(false, 8); break;
+    case 16: GV_CELL_SCAN(false, 16); break;
+    case 32: GV_CELL_SCAN(false, 32); break;
+    default: throw DevErr{GV_EINVAL};
   }
+#undef GV_CELL_SCAN
+  HIPCHK(hipGetLastError());
+  dfree(X, itemcnt);
+  dfree(X, itemw);
 }
 
 // One expansion: incidence test and per-child counts, pruning against the
@@ -1234,21 +1216,19 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
   pa->own_ents = own_ents;
   pa->unit = b.unit;
   uint32_t* ccnt = nullptr;
-  uint32_t* itemcnt = nullptr;
   if (counted) {
     const Counts c = X.counts;
     X.counts = Counts{};
     pa->items = c.items;
     pa->nitems = c.nitems;
     pa->max_items = c.max_items;
-    pa->istride = (uint32_t)c.max_items;
     pa->ioff = c.ioff;
     pa->itemoff = c.itemoff;
     pa->masks = c.masks;
     pa->cnent = c.cnent;
     ccnt = c.ccnt;
   } else {
-    count_pass<FAM, E, M>(X, b, pa, ccnt, itemcnt);
+    count_pass<FAM, E, M>(X, b, pa, ccnt);
   }
 
   if (dive && !leaf) {
@@ -1273,11 +1253,6 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
     }
     k_tot_from<<<1, 64, 0, X.st>>>(nkept, pa->soff + nkept, X.dtot);
     dfree(X, sn);
-    if (itemcnt) {  // POSE4DOF: child-major offsets for k_compact
-      pa->itemoff = dalloc<uint64_t>(X, (uint64_t)nch * pa->istride);
-      excl_scan(X, itemcnt, pa->itemoff, (uint64_t)nch * pa->istride);
-      dfree(X, itemcnt);
-    }
     if (lend) {
       pa->lent = true;
       X.counts = Counts{true, pa->items, pa->nitems, pa->max_items, pa->ioff, pa->itemoff, pa->masks, ccnt, pa->cnent};
@@ -1353,14 +1328,8 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
     dfree(X, keepf);
     dfree(X, keepscan);
     dfree(X, ccnt);
-    dfree(X, itemcnt);
     free_parent(X, pa);
     return nullptr;
-  }
-  if (itemcnt) {  // POSE4DOF: child-major offsets for k_compact
-    pa->itemoff = dalloc<uint64_t>(X, (uint64_t)nch * pa->istride);
-    excl_scan(X, itemcnt, pa->itemoff, (uint64_t)nch * pa->istride);
-    dfree(X, itemcnt);
   }
   pa->nkept = (uint32_t)nkept;
   uint32_t* kcnt = dalloc<uint32_t>(X, nkept);
@@ -1615,9 +1584,9 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
     X.stats.compact_bytes += nb.nent * sizeof(EO);
     X.stats.compact_write_bytes += nb.nent * sizeof(EO);
     if constexpr (fam_masked(FAM)) {
-      k_compact<FAM, E, EO, M, true><<<grid, 256, 0, X.st>>>(
-          lv, pa->cells, pa->items, pa->nitems, pa->ioff, pa->itemoff, pa->istride, (const E*)pa->ents,
-          (const M*)pa->masks, pa->rank_of, r0, r1, keepc, coff, (EO*)nb.ents, X.dovf);
+      k_compact<E, EO, M><<<grid, 256, 0, X.st>>>(lv, pa->items, pa->nitems, pa->itemoff, (const E*)pa->ents,
+                                                  (const M*)pa->masks, pa->rank_of, r0, r1, keepc, coff,
+                                                  (EO*)nb.ents);
     } else {
 #define GV_COMPACT_LIN(N)                                                                                         \
   k_compact_lin<FAM, E, EO, N><<<grid, 256, 0, X.st>>>(lv, (const CWork<N>*)work, nwork, (const E*)pa->ents,      \
@@ -1850,7 +1819,6 @@ void epoch_begin(Run& X) {
   if (const char* e = std::getenv("GV_SUBTREE_FROM")) X.subtree_from = atoi(e);
   if (X.subtree_from < 0) X.subtree_from = std::max(1, X.P0.Lstar + X.subtree_from);
   X.dtot = X.hpin_dev ? X.hpin_dev : dalloc<uint64_t>(X, 4);
-  X.dummy = dalloc<uint32_t>(X, 64);
   X.dreads = dalloc<unsigned long long>(X, 1);
   X.dovf = dalloc<int>(X, 1);
   X.pack_from = 1 << 30;
@@ -2516,7 +2484,6 @@ void epoch_release(Run& X) {
   dfree(X, X.dtests);
   X.dtests = nullptr;
   if (X.dtot != X.hpin_dev) dfree(X, X.dtot);
-  dfree(X, X.dummy);
   dfree(X, X.dreads);
   dfree(X, X.dovf);
   dfree(X, X.dooff);
@@ -2524,7 +2491,6 @@ void epoch_release(Run& X) {
   X.dbest = nullptr;
   X.drecheck = nullptr;
   X.dtot = nullptr;
-  X.dummy = nullptr;
   X.dreads = nullptr;
   X.dovf = nullptr;
   X.dooff = nullptr;
