@@ -26,37 +26,26 @@ __device__ inline uint32_t mbcnt64(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// ---------------------------------------------------------------------------
 // Items: per cell ceil(len / 2^ilog) work items of 2^ilog entries (the last
 // one ragged).
-// ---------------------------------------------------------------------------
 __device__ inline uint32_t items_of(uint32_t len, uint32_t ilog) { return (len + (1u << ilog) - 1u) >> ilog; }
-__global__ void k_item_counts(const Cell* __restrict__ cells, uint32_t ncell, uint32_t ilog,
-                              uint32_t* __restrict__ nitem) {
-  uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < ncell) nitem[c] = items_of(cells[c].len, ilog);
-}
-__global__ void k_item_fill(const Cell* __restrict__ cells, uint32_t ncell, uint32_t ilog,
-                            const uint32_t* __restrict__ nitem, const uint32_t* __restrict__ ioff,
-                            Item* __restrict__ items, uint32_t* __restrict__ total) {
-  uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncell) return;
-  uint32_t o = ioff[c], k = nitem[c];
-  const uint64_t off = cells[c].off;
-  const uint32_t len = cells[c].len, isz = 1u << ilog;
-  for (uint32_t j = 0; j < k; j++) items[o + j] = Item{off + (uint64_t)j * isz, c, min(isz, len - j * isz)};
-  if (c == ncell - 1) *total = o + k;
-}
 
 // ---------------------------------------------------------------------------
-// Single-workgroup forms of the frontier bookkeeping for small batches: one
-// launch where the general form takes a device-wide scan (two launches) and
-// the small kernels around it.  1024 threads; thread t owns the contiguous
-// run [t * GV_SMALL_PER, (t + 1) * GV_SMALL_PER) of the array.  Totals that
-// the host reads go to host-coherent memory, fenced at system scope.
+// Frontier bookkeeping: prefix sums with the work around them in the same
+// kernel, each thread owning PER consecutive elements.  An array that one
+// workgroup of 1024 threads covers (GV_SMALL_N elements) takes one launch; a
+// longer one takes two of the same kernel in workgroups of GV_FRONT_WG:
+// WRITE = false leaves each workgroup's sums in part[], WRITE = true adds up
+// those of the workgroups before it and writes.  (Large workgroups there
+// waited for sixteen free wave slots of one CU while other lanes' kernels
+// ran: 69 us a k_front on the served problems.)  Totals that the host reads
+// go to host-coherent memory, fenced at system scope.  The device-wide
+// scans, reductions and selections that stood here took 5 to 11 launches an
+// expansion: line2d_10k 1.19 against 1.69 ms, pose5dof_20k 2.73 against 2.96.
 // ---------------------------------------------------------------------------
 #define GV_SMALL_PER 4
 #define GV_SMALL_N (1024u * GV_SMALL_PER)
+#define GV_FRONT_WG 256u
 
 // Exclusive prefix of the per-thread values s over the workgroup (wsum: 16
 // slots of LDS); every thread also gets the total.
@@ -106,110 +95,227 @@ __global__ void __launch_bounds__(1024) k_scan_small(const In* __restrict__ in, 
   if (total && threadIdx.x == 0) *total = tot;
 }
 
-// Work items of a batch of at most GV_SMALL_N cells: per-cell item counts,
-// their offsets and the items themselves, in one launch.
-__global__ void __launch_bounds__(1024) k_items_small(const Cell* __restrict__ cells, uint32_t ncell,
-                                                      uint32_t ilog, uint32_t* __restrict__ ioff,
-                                                      Item* __restrict__ items, uint32_t* __restrict__ total) {
-  __shared__ uint32_t wsum[16];
-  const uint32_t b = threadIdx.x * GV_SMALL_PER;
-  uint64_t off[GV_SMALL_PER];
-  uint32_t len[GV_SMALL_PER];
-  uint32_t s = 0;
-#pragma unroll
-  for (int j = 0; j < GV_SMALL_PER; j++) {  // every load issued before any is used
-    const bool in = b + j < ncell;
-    off[j] = in ? cells[b + j].off : 0ull;
-    len[j] = in ? cells[b + j].len : 0u;
+// sums of one workgroup's elements (n: a count, e: list entries)
+struct FSum {
+  uint64_t n, e;
+};
+
+// Exclusive prefixes of every thread's sums (n, e) over all workgroups, and
+// the totals up to and including this workgroup; WRITE = false: leaves this
+// workgroup's sums in part[] instead.
+template <bool WRITE>
+__device__ inline void grid_excl(uint64_t& n, uint64_t& e, FSum& upto, const FSum* part_in, FSum* part_out) {
+  __shared__ uint64_t ws[16];
+  uint64_t tn, te;
+  const uint64_t xn = block_excl<uint64_t>(n, ws, tn), xe = block_excl<uint64_t>(e, ws, te);
+  if constexpr (!WRITE) {
+    if (threadIdx.x == 0) part_out[blockIdx.x] = FSum{tn, te};
+    return;
   }
-#pragma unroll
-  for (int j = 0; j < GV_SMALL_PER; j++) s += items_of(len[j], ilog);
-  uint32_t tot;
-  uint32_t o = block_excl<uint32_t>(s, wsum, tot);
-#pragma unroll
-  for (int j = 0; j < GV_SMALL_PER; j++) {
-    if (b + j >= ncell) break;
-    const uint32_t k = items_of(len[j], ilog), isz = 1u << ilog;
-    ioff[b + j] = o;
-    for (uint32_t i = 0; i < k; i++) items[o + i] = Item{off[j] + (uint64_t)i * isz, b + j, min(isz, len[j] - i * isz)};
-    o += k;
+  uint64_t bn = 0, be = 0;
+  if (gridDim.x > 1) {
+    uint64_t sn = 0, se = 0;
+    for (uint32_t k = threadIdx.x; k < blockIdx.x; k += blockDim.x) {
+      sn += part_in[k].n;
+      se += part_in[k].e;
+    }
+    (void)block_excl<uint64_t>(sn, ws, bn);
+    (void)block_excl<uint64_t>(se, ws, be);
   }
-  if (threadIdx.x == 0) *total = tot;
+  n = bn + xn;
+  e = be + xe;
+  upto = FSum{bn + tn, be + te};
 }
 
-// Prune tail of a small expansion: keepscan = exclusive prefix of keepf,
-// tot[0] = kept children, tot[1] = their entries, tot[2] = the first
-// problem's best key (host-coherent memory).
-__global__ void __launch_bounds__(1024) k_keep_small(const uint32_t* __restrict__ keepf,
-                                                     const uint64_t* __restrict__ keptn, uint32_t nk,
-                                                     const unsigned long long* __restrict__ best,
-                                                     uint32_t* __restrict__ keepscan, uint64_t* tot) {
-  __shared__ uint32_t wsum[16];
-  __shared__ uint64_t wsum64[16];
-  const uint32_t b = threadIdx.x * GV_SMALL_PER;
-  uint32_t v[GV_SMALL_PER];
-  uint32_t s = 0;
-  uint64_t e = 0;
+// Work items of a batch: per-cell item counts, their offsets and the items.
+// The workgroup's items are filled by all its threads (an item's cell found
+// by bisection), so that a few long cells cost no serial loop.
+template <int PER, bool WRITE>
+__global__ void __launch_bounds__(1024) k_items(const Cell* __restrict__ cells, uint32_t ncell, uint32_t ilog,
+                                                FSum* part, uint32_t* __restrict__ ioff, Item* __restrict__ items,
+                                                uint32_t* __restrict__ total) {
+  __shared__ uint32_t loc[1024 * PER];  // first item of the workgroup's cells, from its own first
+  const uint32_t c0 = blockIdx.x * blockDim.x * PER, b = threadIdx.x * PER;
+  uint32_t k[PER];
+  uint64_t s = 0, e = 0;
 #pragma unroll
-  for (int j = 0; j < GV_SMALL_PER; j++) {
-    v[j] = b + j < nk ? keepf[b + j] : 0u;
-    e += b + j < nk ? keptn[b + j] : 0ull;
-    s += v[j];
-  }
-  uint32_t kt;
-  uint64_t et;
-  uint32_t run = block_excl<uint32_t>(s, wsum, kt);
-  (void)block_excl<uint64_t>(e, wsum64, et);
+  for (int j = 0; j < PER; j++) k[j] = c0 + b + j < ncell ? items_of(cells[c0 + b + j].len, ilog) : 0u;
 #pragma unroll
-  for (int j = 0; j < GV_SMALL_PER; j++) {
-    if (b + j < nk) keepscan[b + j] = run;
-    run += v[j];
-  }
-  if (threadIdx.x == 0) {
-    tot[0] = kt;
-    tot[1] = et;
-    tot[2] = best[0];
-    __threadfence_system();
+  for (int j = 0; j < PER; j++) s += k[j];
+  FSum upto{};
+  grid_excl<WRITE>(s, e, upto, part, part);
+  if constexpr (WRITE) {
+    __shared__ uint32_t s_first;
+    if (threadIdx.x == 0) s_first = (uint32_t)s;
+    __syncthreads();
+    const uint32_t first = s_first, n = (uint32_t)upto.n - first;
+    uint32_t o = (uint32_t)s;
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+      loc[b + j] = o - first;
+      if (c0 + b + j < ncell) ioff[c0 + b + j] = o;
+      o += k[j];
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+      uint32_t lo = 0, hi = blockDim.x * PER;  // last cell with loc <= i (cells without items share their successor's)
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (loc[mid] <= i) lo = mid;
+        else hi = mid;
+      }
+      const uint32_t c = c0 + lo, at = (i - loc[lo]) << ilog;
+      items[first + i] = Item{cells[c].off + at, c, min(1u << ilog, cells[c].len - at)};
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = (uint32_t)upto.n;
   }
 }
 
-// Chunk totals of a small chunk: cidx / coff = exclusive prefixes of keepc /
-// csize, tot[0] = kept cells, tot[1] = their entries (host-coherent memory).
-__global__ void __launch_bounds__(1024) k_chunk_small(const uint32_t* __restrict__ keepc,
-                                                      const uint64_t* __restrict__ csize, uint32_t nr,
-                                                      uint32_t* __restrict__ cidx, uint64_t* __restrict__ coff,
-                                                      uint64_t* tot) {
-  __shared__ uint32_t wsum[16];
-  __shared__ uint64_t wsum64[16];
-  const uint32_t b = threadIdx.x * GV_SMALL_PER;
+// Pruning against the best key (counts only shrink down the tree, so a cell
+// whose best possible key cannot beat the best leaf found so far is dropped)
+// of a batch's nk children: the kept ones in parent order with their counts,
+// list offsets and ranks, and the totals (kept children, their entries, the
+// first problem's best key).
+// key = count * 2^B + (2^B - 1 - leaf index): largest count, lowest index.
+template <bool WRITE>
+__global__ void __launch_bounds__(1024) k_front(LevelC lv, int B, uint64_t idxmask, const Cell* __restrict__ cells,
+                                                uint64_t nk, const uint32_t* __restrict__ ccnt,
+                                                const uint32_t* __restrict__ cnent,
+                                                const unsigned long long* __restrict__ best, FSum* part,
+                                                uint32_t* __restrict__ order, uint32_t* __restrict__ scount,
+                                                uint32_t* __restrict__ rank_of, uint64_t* __restrict__ soff,
+                                                uint64_t* tot) {
+  const uint64_t b = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * GV_SMALL_PER;
+  uint32_t cnt[GV_SMALL_PER], ent[GV_SMALL_PER], keep = 0;
+  uint64_t n = 0, e = 0;
+#pragma unroll
+  for (int j = 0; j < GV_SMALL_PER; j++) {
+    cnt[j] = b + j < nk ? ccnt[b + j] : 0u;
+    ent[j] = b + j < nk ? cnent[b + j] : 0u;
+  }
+#pragma unroll
+  for (int j = 0; j < GV_SMALL_PER; j++) {
+    if (b + j >= nk) break;
+    const Cell& C = cells[(b + j) >> lv.abits];
+    const uint64_t pre = (C.prefix << lv.abits) | ((b + j) & ((1u << lv.abits) - 1u));
+    const uint64_t key = ((uint64_t)cnt[j] << B) | (idxmask - (pre << lv.rem_next));
+    if (key > best[C.prob]) {
+      keep |= 1u << j;
+      n++;
+      e += ent[j];
+    }
+  }
+  FSum upto{};
+  grid_excl<WRITE>(n, e, upto, part, part);
+  if constexpr (WRITE) {
+#pragma unroll
+    for (int j = 0; j < GV_SMALL_PER; j++) {
+      if (b + j >= nk) break;
+      const bool kp = (keep >> j) & 1u;
+      rank_of[b + j] = kp ? (uint32_t)n : 0xffffffffu;
+      if (!kp) continue;
+      order[n] = (uint32_t)(b + j);
+      scount[n] = cnt[j];
+      soff[n] = e;
+      n++;
+      e += ent[j];
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+      soff[upto.n] = upto.e;
+      tot[0] = upto.n;
+      tot[1] = upto.e;
+      tot[2] = best[0];
+      __threadfence_system();
+    }
+  }
+}
+
+// Greedy dive above the leaves: every cell keeps its best child (count, then
+// lowest digit), in parent order, so rank r is cell r.
+template <bool WRITE>
+__global__ void __launch_bounds__(1024) k_pick(LevelC lv, uint32_t ncell, const uint32_t* __restrict__ ccnt,
+                                               const uint32_t* __restrict__ cnent, FSum* part,
+                                               uint32_t* __restrict__ order, uint32_t* __restrict__ scount,
+                                               uint32_t* __restrict__ rank_of, uint64_t* __restrict__ soff,
+                                               uint64_t* tot) {
+  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x, nch = 1u << lv.abits;
+  const uint64_t o = (uint64_t)c << lv.abits;
+  uint32_t bc = 0, bd = 0;
+  uint64_t n = 0, e = 0;
+  if (c < ncell) {
+    for (uint32_t ch = 0; ch < nch; ch++)
+      if (ch == 0 || ccnt[o + ch] > bc) { bc = ccnt[o + ch]; bd = ch; }
+    n = 1;
+    e = cnent[o + bd];
+  }
+  FSum upto{};
+  grid_excl<WRITE>(n, e, upto, part, part);
+  if constexpr (WRITE) {
+    if (c < ncell) {
+      for (uint32_t ch = 0; ch < nch; ch++) rank_of[o + ch] = ch == bd ? c : 0xffffffffu;
+      order[c] = (uint32_t)(o + bd);
+      scount[c] = bc;
+      soff[c] = e;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+      soff[ncell] = upto.e;
+      tot[0] = ncell;
+      tot[1] = upto.e;
+      tot[2] = 0;
+      __threadfence_system();
+    }
+  }
+}
+
+// Offsets of a re-cut chunk of nr children (keepc, csize as k_chunk_keep and
+// the probe leave them): each one's cell index and list offset, and the
+// totals tot[0], tot[1] (kept cells, their entries).  With nwork (linear
+// families), tot[2], tot[3] = the items the chunk [r0, r0 + nr) can draw from:
+// in parent order (sorted == 0) its children belong to a contiguous range of
+// parent cells, in count order to any.
+template <bool WRITE>
+__global__ void __launch_bounds__(1024) k_cut(const uint32_t* __restrict__ keepc, const uint64_t* __restrict__ csize,
+                                              uint32_t nr, FSum* part, uint32_t* __restrict__ cidx,
+                                              uint64_t* __restrict__ coff, const uint32_t* __restrict__ order,
+                                              uint32_t r0, int abits, const uint32_t* __restrict__ ioff,
+                                              uint32_t ncell, const uint32_t* __restrict__ nitems_p, int sorted,
+                                              int linear, uint64_t* tot) {
+  const uint32_t b = (blockIdx.x * blockDim.x + threadIdx.x) * GV_SMALL_PER;
   uint32_t v[GV_SMALL_PER];
-  uint64_t z[GV_SMALL_PER];
-  uint32_t s = 0;
-  uint64_t e = 0;
+  uint64_t z[GV_SMALL_PER], n = 0, e = 0;
 #pragma unroll
   for (int j = 0; j < GV_SMALL_PER; j++) {
     v[j] = b + j < nr ? keepc[b + j] : 0u;
     z[j] = b + j < nr ? csize[b + j] : 0ull;
-    s += v[j];
+    n += v[j];
     e += z[j];
   }
-  uint32_t kt;
-  uint64_t et;
-  uint32_t run = block_excl<uint32_t>(s, wsum, kt);
-  uint64_t run64 = block_excl<uint64_t>(e, wsum64, et);
+  FSum upto{};
+  grid_excl<WRITE>(n, e, upto, part, part);
+  if constexpr (WRITE) {
 #pragma unroll
-  for (int j = 0; j < GV_SMALL_PER; j++) {
-    if (b + j < nr) {
-      cidx[b + j] = run;
-      coff[b + j] = run64;
+    for (int j = 0; j < GV_SMALL_PER; j++) {
+      if (b + j < nr) {
+        cidx[b + j] = (uint32_t)n;
+        coff[b + j] = e;
+      }
+      n += v[j];
+      e += z[j];
     }
-    run += v[j];
-    run64 += z[j];
-  }
-  if (threadIdx.x == 0) {
-    tot[0] = kt;
-    tot[1] = et;
-    __threadfence_system();
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+      tot[0] = upto.n;
+      tot[1] = upto.e;
+      if (linear) {
+        tot[2] = 0;
+        tot[3] = *nitems_p;
+        if (!sorted && nr > 0) {
+          const uint32_t c0 = order[r0] >> abits, c1 = order[r0 + nr - 1] >> abits;
+          tot[2] = ioff[c0];
+          if (c1 + 1 < ncell) tot[3] = ioff[c1 + 1];
+        }
+      }
+      __threadfence_system();
+    }
   }
 }
 
@@ -702,12 +808,6 @@ __global__ void __launch_bounds__(256, 4) k_count_pose(const ProbC* __restrict__
   if (lane_id() == 0 && tot) atomicAdd(rechecks, (unsigned long long)tot);
 }
 
-// ---------------------------------------------------------------------------
-// Pruning against the best key (counts only shrink down the tree, so a cell
-// whose best possible key cannot beat the best leaf found so far is dropped)
-// and, at the last level, the best-key reduction (u64 atomic max).
-// key = count * 2^B + (2^B - 1 - leaf index): largest count, lowest index.
-// ---------------------------------------------------------------------------
 // Best-key update of a wave's leaf keys: when every active lane belongs to
 // one problem (the usual case) the wave reduces its maximum first and one
 // lane issues the atomic; otherwise every lane does.  Every lane of the wave
@@ -731,38 +831,21 @@ __device__ inline void wave_best_max(unsigned long long* __restrict__ best, uint
   }
 }
 
-__global__ void k_prune(LevelC lv, int B, uint64_t idxmask, int leaf, const Cell* __restrict__ cells, uint32_t ncell,
-                        const uint32_t* __restrict__ ccnt, const uint32_t* __restrict__ cnent,
-                        unsigned long long* __restrict__ best, uint32_t* __restrict__ keepf,
-                        uint64_t* __restrict__ keptn) {
-  const uint32_t nch = 1u << lv.abits;
+// Best-key reduction over the leaves below a batch's last-level cells (u64
+// atomic max).  key as in k_front.
+__global__ void k_leaf_best(LevelC lv, int B, uint64_t idxmask, const Cell* __restrict__ cells, uint64_t nk,
+                            const uint32_t* __restrict__ ccnt, unsigned long long* __restrict__ best) {
   const uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t nk = (uint64_t)ncell * nch;
-  if (leaf) {  // (uniform: the whole wave stays for the reduction)
-    const bool act = k < nk;
-    uint64_t key = 0;
-    uint32_t prob = 0;
-    if (act) {
-      const uint32_t c = (uint32_t)(k / nch), ch = (uint32_t)(k % nch);
-      const uint64_t pre = (cells[c].prefix << lv.abits) | ch;
-      key = ((uint64_t)ccnt[k] << B) | (idxmask - (pre << lv.rem_next));
-      prob = cells[c].prob;
-    }
-    wave_best_max(best, prob, key, act);
-    return;
+  const bool act = k < nk;  // (the whole wave stays for the reduction)
+  uint64_t key = 0;
+  uint32_t prob = 0;
+  if (act) {
+    const Cell& C = cells[k >> lv.abits];
+    const uint64_t pre = (C.prefix << lv.abits) | (k & ((1u << lv.abits) - 1u));
+    key = ((uint64_t)ccnt[k] << B) | (idxmask - (pre << lv.rem_next));
+    prob = C.prob;
   }
-  if (k >= nk) return;
-  const uint32_t c = (uint32_t)(k / nch), ch = (uint32_t)(k % nch);
-  const Cell& C = cells[c];
-  const uint64_t pre = (C.prefix << lv.abits) | ch;
-  const uint64_t idxmin = pre << lv.rem_next;
-  const uint64_t key = ((uint64_t)ccnt[k] << B) | (idxmask - idxmin);
-  unsigned long long* bp = &best[C.prob];
-  {
-    const uint32_t keep = key > *bp ? 1u : 0u;
-    keepf[k] = keep;
-    keptn[k] = keep ? (uint64_t)cnent[k] : 0ull;
-  }
+  wave_best_max(best, prob, key, act);
 }
 
 // Threshold reporting at the last level: every leaf whose key exceeds its
@@ -788,93 +871,11 @@ __global__ void k_report_leaves(LevelC lv, int B, uint64_t idxmask, const Cell* 
   }
 }
 
-// Greedy dive: in every cell keep only the best child (count, then lowest
-// digit); at the last level record its key.
-__global__ void k_pick_best(LevelC lv, int B, uint64_t idxmask, int leaf, const Cell* __restrict__ cells,
-                            uint32_t ncell, const uint32_t* __restrict__ ccnt, const uint32_t* __restrict__ cnent,
-                            unsigned long long* __restrict__ best, uint32_t* __restrict__ keepf,
-                            uint64_t* __restrict__ keptn) {
-  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  const bool act = c < ncell;
-  const uint32_t nch = 1u << lv.abits;
-  const uint64_t o = (uint64_t)c * nch;
-  uint32_t bc = 0, bd = 0;
-  if (act) {
-    for (uint32_t ch = 0; ch < nch; ch++)
-      if (ch == 0 || ccnt[o + ch] > bc) { bc = ccnt[o + ch]; bd = ch; }
-    for (uint32_t ch = 0; ch < nch; ch++) {
-      keepf[o + ch] = (ch == bd) ? 1u : 0u;
-      keptn[o + ch] = (ch == bd) ? (uint64_t)cnent[o + ch] : 0ull;
-    }
-  }
-  if (leaf) {  // (uniform: the whole wave stays for the reduction)
-    uint64_t key = 0;
-    uint32_t prob = 0;
-    if (act) {
-      const uint64_t pre = (cells[c].prefix << lv.abits) | bd;
-      key = ((uint64_t)bc << B) | (idxmask - (pre << lv.rem_next));
-      prob = cells[c].prob;
-    }
-    wave_best_max(best, prob, key, act);
-  }
-}
-
-// Greedy dive above the leaves: every cell keeps its best child, in parent
-// order, so rank r is cell r.  Writes the kept list directly: order (child
-// index), count, entries, and each child's rank (~0 for the dropped ones).
-__global__ void k_pick_kept(LevelC lv, uint32_t ncell, const uint32_t* __restrict__ ccnt,
-                            const uint32_t* __restrict__ cnent, uint32_t* __restrict__ order,
-                            uint32_t* __restrict__ scount, uint32_t* __restrict__ sn, uint32_t* __restrict__ rank_of) {
-  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncell) return;
-  const uint32_t nch = 1u << lv.abits;
-  const uint64_t o = (uint64_t)c * nch;
-  uint32_t bc = 0, bd = 0;
-  for (uint32_t ch = 0; ch < nch; ch++)
-    if (ch == 0 || ccnt[o + ch] > bc) { bc = ccnt[o + ch]; bd = ch; }
-  for (uint32_t ch = 0; ch < nch; ch++) rank_of[o + ch] = ch == bd ? c : 0xffffffffu;
-  order[c] = (uint32_t)(o + bd);
-  scount[c] = bc;
-  sn[c] = cnent[o + bd];
-}
-
-// the host's totals from a scan's last value: out[0] = n, out[1] = *sum
-// (host-coherent memory)
-__global__ void k_tot_from(uint64_t n, const uint64_t* __restrict__ sum, uint64_t* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    out[0] = n;
-    out[1] = *sum;
-    __threadfence_system();
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Ordering of kept children: highest count first (radix sort on the host
-// side), so the first descent of the depth-first search follows the most
-// promising cells like a beam and reaches a strong lower bound early.
+// Count order of kept children (radix sort on the host side), so the first
+// descent of the depth-first search follows the most promising cells like a
+// beam and reaches a strong lower bound early.
 // ---------------------------------------------------------------------------
-__global__ void k_select_kept(const uint32_t* __restrict__ keepf, const uint32_t* __restrict__ keepscan,
-                              const uint32_t* __restrict__ ccnt, uint64_t nk, uint32_t* __restrict__ kcnt,
-                              uint32_t* __restrict__ kid, uint32_t* __restrict__ rank_of) {
-  const uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < nk) rank_of[k] = 0xffffffffu;  // k_rank fills in the kept children
-  if (k < nk && keepf[k]) {
-    kcnt[keepscan[k]] = ccnt[k];
-    kid[keepscan[k]] = (uint32_t)k;
-  }
-}
-
-// totals of a large expansion, as k_keep_small writes them
-__global__ void k_kept_total(const uint32_t* keepf, const uint32_t* keepscan, uint64_t nk, const uint64_t* esum,
-                             const unsigned long long* best, uint64_t* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    out[0] = nk ? (uint64_t)keepscan[nk - 1] + keepf[nk - 1] : 0;
-    out[1] = *esum;
-    out[2] = best[0];
-    __threadfence_system();
-  }
-}
-
 // rank_of[k] = position of child k in the sorted order; sn[r] = its entries
 __global__ void k_rank(const uint32_t* __restrict__ order, uint32_t nkept, const uint32_t* __restrict__ cnent,
                        const uint32_t* __restrict__ ccnt, uint32_t* __restrict__ rank_of, uint32_t* __restrict__ sn,
@@ -919,29 +920,21 @@ __global__ void k_gather_u64(const uint64_t* __restrict__ a, uint64_t n, uint64_
 
 // Re-cut a pending chunk [r0, r1) against the current bounds: a child is
 // kept only if its count can still reach the best leaf of its own problem.
-// keepc / csize are chunk-local (index r - r0).
-// keep_all: no re-cut (a chunk materialized right after its parent's
-// pruning, whose bounds cannot have moved; its sizes are then known).
+// keepc / csize are chunk-local (index r - r0).  A chunk of every kept child
+// that is materialized right after its parent's pruning is not re-cut (no
+// bound has moved): the kernels below then take keepc = nullptr, and the
+// parent's list offsets for coff.
 __global__ void k_chunk_keep(const uint32_t* __restrict__ order, const uint32_t* __restrict__ scount,
                              const Cell* __restrict__ cells, uint32_t nch, const unsigned long long* __restrict__ best,
                              int B, uint32_t r0, uint32_t r1, const uint32_t* __restrict__ cnent,
-                             uint32_t* __restrict__ keepc, uint64_t* __restrict__ csize, int keep_all) {
+                             uint32_t* __restrict__ keepc, uint64_t* __restrict__ csize) {
   const uint32_t r = r0 + blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= r1) return;
   const uint32_t k = order[r];
   const uint64_t bc = (uint64_t)(best[cells[k / nch].prob] >> B);
-  const uint32_t keep = (keep_all || (uint64_t)scount[r] >= bc) ? 1u : 0u;
+  const uint32_t keep = (uint64_t)scount[r] >= bc ? 1u : 0u;
   keepc[r - r0] = keep;
   csize[r - r0] = keep ? (uint64_t)cnent[k] : 0ull;
-}
-
-__global__ void k_chunk_totals(const uint32_t* keepc, const uint32_t* cidx, const uint64_t* csize,
-                               const uint64_t* coff, uint32_t n, uint64_t* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    out[0] = n ? (uint64_t)cidx[n - 1] + keepc[n - 1] : 0;
-    out[1] = n ? coff[n - 1] + csize[n - 1] : 0;
-    __threadfence_system();
-  }
 }
 
 // entries of the parent cells that have a child in [r0, r1): what one
@@ -956,7 +949,7 @@ __global__ void k_chunk_reads(const Cell* __restrict__ cells, uint32_t ncell, ui
     bool hit = false;
     for (uint32_t ch = 0; ch < nch; ch++) {
       const uint32_t r = rank_of[(uint64_t)c * nch + ch];
-      hit = hit || (r >= r0 && r < r1 && keepc[r - r0]);
+      hit = hit || (r >= r0 && r < r1 && (!keepc || keepc[r - r0]));
     }
     v = hit ? (uint64_t)cells[c].len * bits_per_entry : 0;
   }
@@ -964,13 +957,16 @@ __global__ void k_chunk_reads(const Cell* __restrict__ cells, uint32_t ncell, ui
   if ((threadIdx.x & 63u) == 0 && v) atomicAdd(acc, (unsigned long long)v);
 }
 
-// cells of a materialized chunk, in rank order
+// cells of a materialized chunk, in rank order; also clears the counter of
+// the compaction's work list
 __global__ void k_emit_ranked(LevelC lv, const Cell* __restrict__ cells, const uint32_t* __restrict__ order,
                               uint32_t r0, uint32_t r1, const uint32_t* __restrict__ keepc,
                               const uint32_t* __restrict__ cidx, const uint64_t* __restrict__ coff,
-                              const uint32_t* __restrict__ cnent, Cell* __restrict__ out) {
+                              const uint32_t* __restrict__ cnent, Cell* __restrict__ out,
+                              uint32_t* __restrict__ nwork) {
   const uint32_t r = r0 + blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= r1 || !keepc[r - r0]) return;
+  if (nwork && r == r0) *nwork = 0;
+  if (r >= r1 || (keepc && !keepc[r - r0])) return;
   const uint32_t nch = 1u << lv.abits;
   const uint32_t k = order[r];
   const uint32_t c = k / nch, ch = k % nch;
@@ -984,7 +980,7 @@ __global__ void k_emit_ranked(LevelC lv, const Cell* __restrict__ cells, const u
   o.sector = P.sector;
   o.prob = P.prob;
   o._pad = 0;
-  out[cidx[r - r0]] = o;
+  out[keepc ? cidx[r - r0] : r - r0] = o;
 }
 
 // ---------------------------------------------------------------------------
@@ -1005,28 +1001,6 @@ template <int NCH> struct CWork {
   uint64_t wpos[NCH];
 };
 
-// Items a chunk [r0, r1) of a parent's kept children can draw from, written
-// to out[0], out[1] (host-coherent memory): in parent order (sorted == 0)
-// the chunk's children belong to a contiguous range of parent cells, so
-// only those cells' items; in count order every item.  Also clears the work
-// list's counter.
-__global__ void k_chunk_range(const uint32_t* __restrict__ order, uint32_t r0, uint32_t r1, uint32_t nch,
-                              const uint32_t* __restrict__ ioff, uint32_t ncell, const uint32_t* __restrict__ nitems_p,
-                              int sorted, uint32_t* __restrict__ nwork, uint64_t* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *nwork = 0;
-    if (sorted || r1 <= r0) {
-      out[0] = 0;
-      out[1] = *nitems_p;
-    } else {
-      const uint32_t c0 = order[r0] / nch, c1 = order[r1 - 1] / nch;
-      out[0] = ioff[c0];
-      out[1] = c1 + 1 < ncell ? ioff[c1 + 1] : *nitems_p;
-    }
-    __threadfence_system();
-  }
-}
-
 // One thread per item of [i0, i1); with acc, also the bits of the entries
 // the compaction reads (items with a kept child in the chunk).
 template <int NCH>
@@ -1045,7 +1019,7 @@ __global__ void k_chunk_work(const Item* __restrict__ items, const uint32_t* __r
 #pragma unroll
     for (int ch = 0; ch < NCH; ch++) {
       const uint32_t r = rank_of[(uint64_t)I.cell * NCH + ch];
-      if (r >= r0 && r < r1 && keepc[r - r0]) {
+      if (r >= r0 && r < r1 && (!keepc || keepc[r - r0])) {
         w.kmask |= 1u << ch;
         w.wpos[ch] = coff[r - r0] + itemoff[(uint64_t)it * NCH + ch];
       }
@@ -1261,7 +1235,7 @@ __global__ void __launch_bounds__(256) k_compact(LevelC lv, const Item* __restri
       wpos[ch] = 0;
       if (ch >= nch) continue;
       const uint32_t r = rank_of[(uint64_t)I.cell * nch + ch];
-      if (r >= r0 && r < r1 && keepc[r - r0]) {
+      if (r >= r0 && r < r1 && (!keepc || keepc[r - r0])) {
         kmask |= 1u << ch;
         wpos[ch] = coff[r - r0] + itemoff[(uint64_t)it * nch + ch];
       }
@@ -1512,10 +1486,9 @@ __global__ void k_group_heads(const uint64_t* __restrict__ keys, const uint32_t*
 
 // one thread per run head: the merged entry carries the run's summed weight
 template <typename E>
-__global__ void k_group_write(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ idx,
-                              const E* __restrict__ ents, uint64_t n, const uint32_t* __restrict__ head,
-                              const uint32_t* __restrict__ hscan, int hb, E* __restrict__ out,
-                              uint32_t* __restrict__ newlen) {
+__global__ void k_group_write(const uint32_t* __restrict__ idx, const E* __restrict__ ents, uint64_t n,
+                              const uint32_t* __restrict__ head, const uint32_t* __restrict__ hscan,
+                              E* __restrict__ out) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n || !head[i]) return;
   uint32_t w = 0;
@@ -1527,15 +1500,28 @@ __global__ void k_group_write(const uint64_t* __restrict__ keys, const uint32_t*
   E e = ents[idx[i]];
   Tuple<E>::setw(e, w);
   out[hscan[i]] = e;
-  const uint32_t c = hb >= 64 ? 0u : (uint32_t)(keys[i] >> hb);
-  atomicAdd(&newlen[c], 1u);
 }
 
-__global__ void k_group_cells(Cell* __restrict__ cells, uint32_t ncell, const uint32_t* __restrict__ newlen,
-                              const uint32_t* __restrict__ newoff) {
+// The cells' merged lists: cell c's run heads are those of its keys' range in
+// the sorted order (found by bisection; a counter per cell took one atomic a
+// head, 116 us for the 2,000 heads of one root cell).
+__global__ void k_group_cells(Cell* __restrict__ cells, uint32_t ncell, const uint64_t* __restrict__ keys, uint64_t n,
+                              int hb, const uint32_t* __restrict__ hscan, uint32_t U) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < ncell) {
-    cells[c].off = newoff[c];
-    cells[c].len = newlen[c];
+  if (c >= ncell) return;
+  uint32_t off[2];
+  for (int s = 0; s < 2; s++) {
+    const uint64_t cc = (uint64_t)c + s;  // first position whose cell is cc or later
+    uint64_t lo = 0, hi = n;
+    if (hb >= 64 || cc >= ncell) lo = cc == 0 ? 0 : n;
+    else
+      while (lo < hi) {
+        const uint64_t mid = lo + (hi - lo) / 2;
+        if ((keys[mid] >> hb) < cc) lo = mid + 1;
+        else hi = mid;
+      }
+    off[s] = lo < n ? hscan[lo] : U;
   }
+  cells[c].off = off[0];
+  cells[c].len = off[1] - off[0];
 }

@@ -1022,14 +1022,8 @@ void group_batch(Run& X, Batch& b, bool own_ents) {
   const uint64_t U = (uint64_t)last[0] + last[1];
   if (U < n) {
     E* out = dalloc<E>(X, U);
-    uint32_t* newlen = dalloc<uint32_t>(X, b.ncell);
-    uint32_t* newoff = dalloc<uint32_t>(X, b.ncell);
-    HIPCHK(hipMemsetAsync(newlen, 0, b.ncell * sizeof(uint32_t), X.st));
-    k_group_write<E><<<nblk(n), 256, 0, X.st>>>(k1, i1, (const E*)b.ents, n, head, hscan, hb, out, newlen);
-    excl_scan(X, newlen, newoff, b.ncell);
-    k_group_cells<<<nblk(b.ncell), 256, 0, X.st>>>(b.cells, b.ncell, newlen, newoff);
-    dfree(X, newlen);
-    dfree(X, newoff);
+    k_group_write<E><<<nblk(n), 256, 0, X.st>>>(i1, (const E*)b.ents, n, head, hscan, out);
+    k_group_cells<<<nblk(b.ncell), 256, 0, X.st>>>(b.cells, b.ncell, k1, n, hb, hscan, (uint32_t)U);
     if (own_ents) dfree(X, b.ents);
     b.ents = out;
     b.nent = U;
@@ -1076,20 +1070,20 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
   if constexpr (FAM == FAM_POSE5DOF)
     if (tcand < 0 && !X.tile_env)
       while (ilog > kItemLogMin5 && (b.nent >> ilog) < (uint64_t)X.ctx->n_cu * kItemsPerCu5) ilog--;
-  uint32_t* nitem = b.ncell <= GV_SMALL_N ? nullptr : dalloc<uint32_t>(X, b.ncell);
   pa->ioff = dalloc<uint32_t>(X, b.ncell);
   pa->max_items = b.ncell + (b.nent >> ilog) + 1;
   pa->items = dalloc<Item>(X, pa->max_items);
   pa->nitems = dalloc<uint32_t>(X, 1);
+  // (one workgroup for a small batch; more of them, a cell per thread, above)
   if (b.ncell <= GV_SMALL_N) {
-    k_items_small<<<1, 1024, 0, X.st>>>(b.cells, b.ncell, ilog, pa->ioff, pa->items, pa->nitems);
+    k_items<GV_SMALL_PER, true><<<1, 1024, 0, X.st>>>(b.cells, b.ncell, ilog, nullptr, pa->ioff, pa->items, pa->nitems);
   } else {
-    HIPCHK(hipMemsetAsync(pa->nitems, 0, sizeof(uint32_t), X.st));
-    k_item_counts<<<nblk(b.ncell), 256, 0, X.st>>>(b.cells, b.ncell, ilog, nitem);
-    excl_scan(X, nitem, pa->ioff, b.ncell);
-    k_item_fill<<<nblk(b.ncell), 256, 0, X.st>>>(b.cells, b.ncell, ilog, nitem, pa->ioff, pa->items, pa->nitems);
+    const unsigned g = nblk(b.ncell, GV_FRONT_WG);
+    FSum* part = dalloc<FSum>(X, g);
+    k_items<1, false><<<g, GV_FRONT_WG, 0, X.st>>>(b.cells, b.ncell, ilog, part, pa->ioff, pa->items, pa->nitems);
+    k_items<1, true><<<g, GV_FRONT_WG, 0, X.st>>>(b.cells, b.ncell, ilog, part, pa->ioff, pa->items, pa->nitems);
+    dfree(X, part);
   }
-  dfree(X, nitem);
   // one row of per-child entries (and weights) per item; the masked families
   // store per-entry pass masks, the linear ones repeat the test in the
   // compaction
@@ -1188,6 +1182,69 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
   dfree(X, itemw);
 }
 
+// Whether every kept child fits the first chunk the schedule would cut (the
+// same rule as plan_chunks, decided from the totals already on the host).
+bool one_chunk(const Run& X, const Parent* pa) {
+  const int lc = std::min(pa->level + 1, X.P0.Lstar - 1);
+  const double per_cell = 64.0 + 40.0 * (double)(1u << X.P0.lev[lc].abits);
+  const double per_ent = (double)X.ent_bytes + 8.0;
+  const uint64_t cap = X.beam ? X.first_cells : (1ull << 30);
+  return (uint64_t)pa->nkept <= cap &&
+         (double)pa->kept_entries * per_ent + (double)pa->nkept * per_cell <= (double)X.chunk_bytes;
+}
+
+// Puts a parent's kept children in descending count order (several problems
+// in a batch: of the count relative to their problem's largest).
+void sort_kept(Run& X, Parent* pa, const uint32_t* ccnt, uint32_t nch) {
+  const uint32_t nkept = pa->nkept;
+  uint32_t* kid = pa->order;
+  uint32_t* key = pa->scount;
+  uint32_t* pmax = nullptr;
+  pa->sorted = true;
+  pa->order = dalloc<uint32_t>(X, nkept);
+  if (X.probs.size() > 1) {
+    pmax = dalloc<uint32_t>(X, X.probs.size());
+    key = dalloc<uint32_t>(X, nkept);
+    HIPCHK(hipMemsetAsync(pmax, 0, X.probs.size() * sizeof(uint32_t), X.st));
+    k_prob_max<<<nblk(nkept), 256, 0, X.st>>>(pa->scount, kid, nkept, pa->cells, nch, pmax);
+    k_prob_norm<<<nblk(nkept), 256, 0, X.st>>>(pa->scount, kid, nkept, pa->cells, nch, pmax, key);
+  }
+  // one problem: the key is a count, at most n, so only its low bits are
+  // sorted (fewer radix passes on small problems)
+  int end_bit = 32;
+  if (!pmax) {
+    end_bit = 1;
+    while (end_bit < 32 && (uint64_t)X.probs[0]->n >> end_bit) end_bit++;
+  }
+  if (nkept <= GV_SMALL_N) {
+    k_sort_desc_small<<<1, 1024, 0, X.st>>>(key, kid, nkept, end_bit, pa->order);
+  } else {
+    uint32_t* skey = dalloc<uint32_t>(X, nkept);
+    size_t tb = 0;
+    HIPCHK(hipcub::DeviceRadixSort::SortPairsDescending(nullptr, tb, key, skey, kid, pa->order, (int)nkept, 0,
+                                                        end_bit, X.st));
+    void* tmp = dalloc<char>(X, tb);
+    HIPCHK(hipcub::DeviceRadixSort::SortPairsDescending(tmp, tb, key, skey, kid, pa->order, (int)nkept, 0, end_bit,
+                                                        X.st));
+    dfree(X, tmp);
+    dfree(X, skey);
+  }
+  if (pmax) {
+    dfree(X, pmax);
+    dfree(X, key);
+  }
+  dfree(X, kid);
+  uint32_t* sn = dalloc<uint32_t>(X, nkept);
+  k_rank<<<nblk(nkept), 256, 0, X.st>>>(pa->order, nkept, pa->cnent, ccnt, pa->rank_of, sn, pa->scount);
+  if (nkept <= GV_SMALL_N) {
+    k_scan_small<uint32_t, uint64_t><<<1, 1024, 0, X.st>>>(sn, pa->soff, nkept, pa->soff + nkept);
+  } else {
+    excl_scan(X, sn, pa->soff, nkept);
+    k_soff_last<<<1, 64, 0, X.st>>>(pa->soff, sn, nkept);
+  }
+  dfree(X, sn);
+}
+
 // One expansion: incidence test and per-child counts, pruning against the
 // best key (or, for the greedy dive, keeping only the best child), then the
 // kept children sorted by count.  Returns nullptr when nothing is kept (or at
@@ -1231,176 +1288,75 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
     count_pass<FAM, E, M>(X, b, pa, ccnt);
   }
 
-  if (dive && !leaf) {
-    // greedy dive: one child per cell in parent order; the kept list is
-    // written directly (no selection scan, no sort), its entries summed by
-    // the offsets' scan
-    const uint32_t nkept = b.ncell;
-    pa->nkept = nkept;
-    pa->sorted = false;
-    pa->order = dalloc<uint32_t>(X, nkept);
-    pa->scount = dalloc<uint32_t>(X, nkept);
-    pa->rank_of = dalloc<uint32_t>(X, nk);
-    uint32_t* sn = dalloc<uint32_t>(X, nkept);
-    k_pick_kept<<<nblk(nkept), 256, 0, X.st>>>(lv, nkept, ccnt, pa->cnent, pa->order, pa->scount, sn, pa->rank_of);
-    if (!lend) dfree(X, ccnt);
-    pa->soff = dalloc<uint64_t>(X, nkept + 1);
-    if (nkept <= GV_SMALL_N) {
-      k_scan_small<uint32_t, uint64_t><<<1, 1024, 0, X.st>>>(sn, pa->soff, nkept, pa->soff + nkept);
-    } else {
-      excl_scan(X, sn, pa->soff, nkept);
-      k_soff_last<<<1, 64, 0, X.st>>>(pa->soff, sn, nkept);
-    }
-    k_tot_from<<<1, 64, 0, X.st>>>(nkept, pa->soff + nkept, X.dtot);
-    dfree(X, sn);
-    if (lend) {
-      pa->lent = true;
-      X.counts = Counts{true, pa->items, pa->nitems, pa->max_items, pa->ioff, pa->itemoff, pa->masks, ccnt, pa->cnent};
-    }
+  if (leaf) {
+    if (X.report)  // (the bound stays fixed)
+      k_report_leaves<<<nblk(nk), 256, 0, X.st>>>(lv, P.B, P.idxmask, b.cells, b.ncell, ccnt, X.dbest, X.rep_idx,
+                                                   X.rep_cnt, X.rep_n, X.rep_cap);
+    else
+      k_leaf_best<<<nblk(nk), 256, 0, X.st>>>(lv, P.B, P.idxmask, b.cells, nk, ccnt, X.dbest);
     HIPCHK(hipGetLastError());
-    uint64_t kt[2];
-    read_tot(X, kt);
-    pa->kept_entries = kt[1];
-    X.stats.cells_pruned += nk - nkept;
-    if (X.trace) {
-      const uint64_t bst = d2h1(X, X.dbest);
-      std::fprintf(stderr, "gv: level %d cells %u entries %llu kept %llu best %llu (dive)%s\n", m, b.ncell,
-                   (unsigned long long)b.nent, (unsigned long long)nkept, (unsigned long long)(bst >> P.B),
-                   (b.unit && m >= X.unit_from) ? " one-word" : (m >= X.pack_from ? " packed" : ""));
-    }
-    return pa;
+    if (!dive) X.beam = false;
+    dfree(X, ccnt);
+    free_parent(X, pa);
+    return nullptr;
   }
-  uint32_t* keepf = dalloc<uint32_t>(X, nk);
-  uint64_t* keptn = dalloc<uint64_t>(X, nk);
+  // the kept children in parent order: the best of every cell (greedy dive),
+  // or those that can still beat the best key
+  const uint64_t nsel = dive ? b.ncell : nk;
+  pa->order = dalloc<uint32_t>(X, nsel);
+  pa->scount = dalloc<uint32_t>(X, nsel);
+  pa->rank_of = dalloc<uint32_t>(X, nk);
+  pa->soff = dalloc<uint64_t>(X, nsel + 1);
+  pa->sorted = false;
+  const unsigned per = dive ? 1u : (unsigned)GV_SMALL_PER;
+  const unsigned wg = nsel <= 1024u * per ? 1024u : GV_FRONT_WG, g = nblk(nsel, wg * per);
+  FSum* part = g > 1 ? dalloc<FSum>(X, g) : nullptr;
   if (dive) {
-    k_pick_best<<<nblk(b.ncell), 256, 0, X.st>>>(lv, P.B, P.idxmask, leaf ? 1 : 0, b.cells, b.ncell, ccnt,
-                                                 pa->cnent, X.dbest, keepf, keptn);
-  } else if (leaf && X.report) {
-    // (the leaves are reported below; the bound stays fixed)
+#define GV_PICK(W)                                                                                              \
+  k_pick<W><<<g, wg, 0, X.st>>>(lv, b.ncell, ccnt, pa->cnent, part, pa->order, pa->scount, pa->rank_of, pa->soff, \
+                                  X.dtot)
+    if (g > 1) GV_PICK(false);
+    GV_PICK(true);
+#undef GV_PICK
   } else {
-    k_prune<<<nblk(nk), 256, 0, X.st>>>(lv, P.B, P.idxmask, leaf ? 1 : 0, b.cells, b.ncell, ccnt, pa->cnent,
-                                        X.dbest, keepf, keptn);
+#define GV_FRONT(W)                                                                                              \
+  k_front<W><<<g, wg, 0, X.st>>>(lv, P.B, P.idxmask, b.cells, nk, ccnt, pa->cnent, X.dbest, part, pa->order,     \
+                                   pa->scount, pa->rank_of, pa->soff, X.dtot)
+    if (g > 1) GV_FRONT(false);
+    GV_FRONT(true);
+#undef GV_FRONT
   }
   HIPCHK(hipGetLastError());
-  if (leaf && X.report) {
-    k_report_leaves<<<nblk(nk), 256, 0, X.st>>>(lv, P.B, P.idxmask, b.cells, b.ncell, ccnt, X.dbest, X.rep_idx,
-                                                 X.rep_cnt, X.rep_n, X.rep_cap);
-    HIPCHK(hipGetLastError());
+  dfree(X, part);
+  if (lend) {
+    pa->lent = true;
+    X.counts = Counts{true, pa->items, pa->nitems, pa->max_items, pa->ioff, pa->itemoff, pa->masks, ccnt, pa->cnent};
   }
-  if (leaf) {
-    dfree(X, keptn);
-    if (!dive) X.beam = false;
-    dfree(X, keepf);
-    dfree(X, ccnt);
-    pa->pending = 0;
-    free_parent(X, pa);
-    return nullptr;
-  }
-  uint32_t* keepscan = dalloc<uint32_t>(X, nk);
-  if (nk <= GV_SMALL_N) {
-    k_keep_small<<<1, 1024, 0, X.st>>>(keepf, keptn, (uint32_t)nk, X.dbest, keepscan, X.dtot);
-  } else {
-    excl_scan(X, keepf, keepscan, nk);
-    uint64_t* esum = dalloc<uint64_t>(X, 1);
-    size_t tb = 0;
-    HIPCHK(hipcub::DeviceReduce::Sum(nullptr, tb, keptn, esum, (int)nk, X.st));
-    void* tmp = dalloc<char>(X, tb);
-    HIPCHK(hipcub::DeviceReduce::Sum(tmp, tb, keptn, esum, (int)nk, X.st));
-    dfree(X, tmp);
-    k_kept_total<<<1, 64, 0, X.st>>>(keepf, keepscan, nk, esum, X.dbest, X.dtot);
-    dfree(X, esum);
-  }
-  dfree(X, keptn);
   uint64_t kt[3];
   read_tot(X, kt, 3);
-  const uint64_t nkept = kt[0];
+  pa->nkept = (uint32_t)kt[0];
   pa->kept_entries = kt[1];
   pa->best = kt[2];
-  X.stats.cells_pruned += nk - nkept;
+  X.stats.cells_pruned += nk - kt[0];
   if (X.trace) {
     const uint64_t bst = d2h1(X, X.dbest);
-    std::fprintf(stderr, "gv: level %d cells %u entries %llu kept %llu best %llu%s%s\n", m, b.ncell,
-                 (unsigned long long)b.nent, (unsigned long long)nkept, (unsigned long long)(bst >> P.B),
-                 dive ? " (dive)" : "",
+    std::fprintf(stderr, "gv: level %d cells %u entries %llu kept %u best %llu%s%s\n", m, b.ncell,
+                 (unsigned long long)b.nent, pa->nkept, (unsigned long long)(bst >> P.B), dive ? " (dive)" : "",
                  (b.unit && m >= X.unit_from) ? " one-word" : (m >= X.pack_from ? " packed" : ""));
   }
-  if (nkept == 0) {
-    dfree(X, keepf);
-    dfree(X, keepscan);
+  if (pa->nkept == 0) {
     dfree(X, ccnt);
     free_parent(X, pa);
     return nullptr;
   }
-  pa->nkept = (uint32_t)nkept;
-  uint32_t* kcnt = dalloc<uint32_t>(X, nkept);
-  uint32_t* kid = dalloc<uint32_t>(X, nkept);
-  pa->rank_of = dalloc<uint32_t>(X, nk);
-  k_select_kept<<<nblk(nk), 256, 0, X.st>>>(keepf, keepscan, ccnt, nk, kcnt, kid, pa->rank_of);
-  dfree(X, keepf);
-  dfree(X, keepscan);
-  // Count order only during the first descent.  After it a chunk is capped
-  // by memory alone, so the kept children of a parent mostly go in one
-  // chunk and their order changes little: the 4-DoF and 5-DoF workloads
-  // count the same tests in parent order, and the sort is saved.  Parent
-  // order also makes a chunk a contiguous range of parents, each read once.
-  // The greedy dive keeps one child per cell and takes them all at once:
-  // parent order, no sort.
-  pa->sorted = !dive && X.beam;
-  pa->scount = dalloc<uint32_t>(X, nkept);
-  if (!pa->sorted) {
-    // after the first descent the bounds are strong: keep parent order so
-    // that a chunk is a contiguous range of parents, each read once
-    pa->order = kid;
-    kid = nullptr;
-  } else {
-    pa->order = dalloc<uint32_t>(X, nkept);
-    uint32_t* key = kcnt;
-    uint32_t* pmax = nullptr;
-    if (X.probs.size() > 1) {
-      pmax = dalloc<uint32_t>(X, X.probs.size());
-      key = dalloc<uint32_t>(X, nkept);
-      HIPCHK(hipMemsetAsync(pmax, 0, X.probs.size() * sizeof(uint32_t), X.st));
-      k_prob_max<<<nblk(nkept), 256, 0, X.st>>>(kcnt, kid, (uint32_t)nkept, b.cells, nch, pmax);
-      k_prob_norm<<<nblk(nkept), 256, 0, X.st>>>(kcnt, kid, (uint32_t)nkept, b.cells, nch, pmax, key);
-    }
-    // one problem: the key is a count, at most n, so only its low bits are
-    // sorted (fewer radix passes on small problems)
-    int end_bit = 32;
-    if (!pmax) {
-      end_bit = 1;
-      while (end_bit < 32 && (uint64_t)X.probs[0]->n >> end_bit) end_bit++;
-    }
-    if (nkept <= GV_SMALL_N) {
-      k_sort_desc_small<<<1, 1024, 0, X.st>>>(key, kid, (uint32_t)nkept, end_bit, pa->order);
-    } else {
-      uint32_t* skey = dalloc<uint32_t>(X, nkept);
-      size_t tb = 0;
-      HIPCHK(hipcub::DeviceRadixSort::SortPairsDescending(nullptr, tb, key, skey, kid, pa->order, (int)nkept, 0,
-                                                           end_bit, X.st));
-      void* tmp = dalloc<char>(X, tb);
-      HIPCHK(hipcub::DeviceRadixSort::SortPairsDescending(tmp, tb, key, skey, kid, pa->order, (int)nkept, 0, end_bit,
-                                                           X.st));
-      dfree(X, tmp);
-      dfree(X, skey);
-    }
-    if (pmax) {
-      dfree(X, pmax);
-      dfree(X, key);
-    }
-  }
-  dfree(X, kcnt);
-  dfree(X, kid);
-  uint32_t* sn = dalloc<uint32_t>(X, nkept);
-  k_rank<<<nblk(nkept), 256, 0, X.st>>>(pa->order, (uint32_t)nkept, pa->cnent, ccnt, pa->rank_of, sn, pa->scount);
-  dfree(X, ccnt);
-  pa->soff = dalloc<uint64_t>(X, nkept + 1);
-  if (nkept <= GV_SMALL_N) {
-    k_scan_small<uint32_t, uint64_t><<<1, 1024, 0, X.st>>>(sn, pa->soff, (uint32_t)nkept, pa->soff + nkept);
-  } else {
-    excl_scan(X, sn, pa->soff, nkept);
-    k_soff_last<<<1, 64, 0, X.st>>>(pa->soff, sn, (uint32_t)nkept);
-  }
-  dfree(X, sn);
+  // Count order only during the first descent, and only where the children
+  // do not all go in one chunk (then every order materializes the same
+  // batch).  After the descent a chunk is capped by memory alone and the
+  // bounds are strong: the 4-DoF and 5-DoF workloads count the same tests in
+  // parent order, the sort is saved, and a chunk is a contiguous range of
+  // parents, each read once.
+  if (!dive && X.beam && !one_chunk(X, pa)) sort_kept(X, pa, ccnt, nch);
+  if (!lend) dfree(X, ccnt);
   return pa;
 }
 
@@ -1498,48 +1454,43 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
   const LevelC lv = P.lev[pa->level];
   const uint32_t nch = 1u << lv.abits;
   const uint32_t nr = r1 - r0;
-  // drop the children that can no longer reach their problem's best leaf
-  uint32_t* keepc = dalloc<uint32_t>(X, nr);
-  uint32_t* cidx = dalloc<uint32_t>(X, nr);
-  uint64_t* csize = dalloc<uint64_t>(X, nr);
-  uint64_t* coff = dalloc<uint64_t>(X, nr);
   // A chunk of every kept child materialized right after its parent's
-  // pruning: no bound has moved since, so nothing is re-cut and its sizes
-  // are the parent's totals (no wait for the device).
-  bool fresh = pa->fresh && r0 == 0 && r1 == pa->nkept;
+  // pruning: no bound has moved since, so nothing is re-cut (keepc = null) and
+  // its sizes are the parent's totals (no wait for the device).  A probe drops
+  // children, so such a chunk counts what is left.
+  const bool probe = probe_fits<FAM, E>(P, pa->level) && want_probe(X, pa);
+  const bool fresh = pa->fresh && r0 == 0 && r1 == pa->nkept && !probe;
   pa->fresh = false;
-  k_chunk_keep<<<nblk(nr), 256, 0, X.st>>>(pa->order, pa->scount, pa->cells, nch, X.dbest, P.B, r0, r1, pa->cnent,
-                                            keepc, csize, fresh ? 1 : 0);
-  if (probe_fits<FAM, E>(P, pa->level) && want_probe(X, pa)) {
-    fresh = false;
-    auto evp = ev_begin(X, 0);
-    X.stats.test_launches++;
-    probe_chunk<FAM, E, M>(X, pa, r0, r1, keepc, csize);
-    ev_end(X, evp);
-    HIPCHK(hipGetLastError());
-  }
-  if (nr <= GV_SMALL_N) {
-    k_chunk_small<<<1, 1024, 0, X.st>>>(keepc, csize, nr, cidx, coff, X.dtot);
-  } else {
-    excl_scan(X, keepc, cidx, nr);
-    excl_scan(X, csize, coff, nr);
-    k_chunk_totals<<<1, 64, 0, X.st>>>(keepc, cidx, csize, coff, nr, X.dtot);
-  }
-  // linear families: the item range the chunk draws from (read with the totals)
   const bool linear = !fam_masked(FAM);
-  uint32_t* nwork = nullptr;
-  if (linear) {
-    nwork = dalloc<uint32_t>(X, 1);
-    k_chunk_range<<<1, 64, 0, X.st>>>(pa->order, r0, r1, nch, pa->ioff, pa->ncell, pa->nitems, pa->sorted ? 1 : 0,
-                                      nwork, X.dtot + 2);
-  }
-  uint64_t tot[4];
-  if (fresh) {
-    tot[0] = pa->nkept;
-    tot[1] = pa->kept_entries;
-    tot[2] = 0;
-    tot[3] = pa->max_items;  // every item (clamped to the count on the device)
-  } else {
+  uint32_t* keepc = nullptr;
+  uint32_t* cidx = nullptr;
+  uint64_t* csize = nullptr;
+  uint64_t* coff = fresh ? pa->soff : nullptr;
+  uint64_t tot[4] = {pa->nkept, pa->kept_entries, 0, pa->max_items};  // fresh: every item (clamped on the device)
+  if (!fresh) {
+    // drop the children that can no longer reach their problem's best leaf
+    keepc = dalloc<uint32_t>(X, nr);
+    cidx = dalloc<uint32_t>(X, nr);
+    csize = dalloc<uint64_t>(X, nr);
+    coff = dalloc<uint64_t>(X, nr);
+    k_chunk_keep<<<nblk(nr), 256, 0, X.st>>>(pa->order, pa->scount, pa->cells, nch, X.dbest, P.B, r0, r1, pa->cnent,
+                                              keepc, csize);
+    if (probe) {
+      auto evp = ev_begin(X, 0);
+      X.stats.test_launches++;
+      probe_chunk<FAM, E, M>(X, pa, r0, r1, keepc, csize);
+      ev_end(X, evp);
+    }
+    const unsigned wg = nr <= GV_SMALL_N ? 1024u : GV_FRONT_WG, g = nblk(nr, wg * GV_SMALL_PER);
+    FSum* part = g > 1 ? dalloc<FSum>(X, g) : nullptr;
+#define GV_CUT(W)                                                                                               \
+  k_cut<W><<<g, wg, 0, X.st>>>(keepc, csize, nr, part, cidx, coff, pa->order, r0, lv.abits, pa->ioff, pa->ncell, \
+                                 pa->nitems, pa->sorted ? 1 : 0, linear ? 1 : 0, X.dtot)
+    if (g > 1) GV_CUT(false);
+    GV_CUT(true);
+#undef GV_CUT
+    HIPCHK(hipGetLastError());
+    dfree(X, part);
     read_tot(X, tot, linear ? 4 : 2);
   }
   bool made = false;
@@ -1550,8 +1501,9 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
     nb.nent = tot[1];
     nb.cells = dalloc<Cell>(X, nb.ncell);
     nb.ents = dalloc<EO>(X, nb.nent);
+    uint32_t* nwork = linear ? dalloc<uint32_t>(X, 1) : nullptr;
     k_emit_ranked<<<nblk(nr), 256, 0, X.st>>>(lv, pa->cells, pa->order, r0, r1, keepc, cidx, coff, pa->cnent,
-                                              nb.cells);
+                                              nb.cells, nwork);
     int cand;
     const int gpc = grid_pick(X, 1, nb.nent * sizeof(EO), &cand);
     const unsigned grid = (unsigned)std::min<uint64_t>((pa->max_items + 3) / 4, (uint64_t)X.ctx->n_cu * gpc);
@@ -1606,14 +1558,14 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
     ev_end(X, evp);
     HIPCHK(hipGetLastError());
     dfree(X, work);
+    dfree(X, nwork);
     nb.unit = pa->unit;
     made = true;
   }
-  dfree(X, nwork);
   dfree(X, keepc);
   dfree(X, cidx);
   dfree(X, csize);
-  dfree(X, coff);
+  if (!fresh) dfree(X, coff);
   if (--pa->pending == 0) free_parent(X, pa);
   if constexpr (std::is_same<EO, EntQ24>::value) {
     // used only where no list is grouped
@@ -1669,17 +1621,6 @@ bool materialize_at(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
   if (pa->level >= X.pack_from) return materialize<FAM, EP, EP, M>(X, pa, r0, r1, nb);
   if (pa->level + 1 >= X.pack_from) return materialize<FAM, E, EP, M>(X, pa, r0, r1, nb);
   return materialize<FAM, E, E, M>(X, pa, r0, r1, nb);
-}
-
-// Whether every kept child fits the first chunk the schedule would cut (the
-// same rule as plan_chunks, decided from the totals already on the host).
-bool one_chunk(const Run& X, const Parent* pa) {
-  const int lc = std::min(pa->level + 1, X.P0.Lstar - 1);
-  const double per_cell = 64.0 + 40.0 * (double)(1u << X.P0.lev[lc].abits);
-  const double per_ent = (double)X.ent_bytes + 8.0;
-  const uint64_t cap = X.beam ? X.first_cells : (1ull << 30);
-  return (uint64_t)pa->nkept <= cap &&
-         (double)pa->kept_entries * per_ent + (double)pa->nkept * per_cell <= (double)X.chunk_bytes;
 }
 
 template <int FAM, typename E, typename M>
@@ -1980,14 +1921,11 @@ void start_search(Run& X) {
       Parent* pa = expand_at<FAM, E, M>(X, b, keep ? false : own, dv, keep);
       if (!pa) break;
       uint32_t r1 = pa->nkept;
-      if (!dv) {
-        if (one_chunk(X, pa)) {
-          pa->fresh = true;
-        } else {
-          std::vector<std::pair<uint32_t, uint32_t>> ch;
-          plan_chunks(X, pa, ch);
-          r1 = ch.front().second;
-        }
+      pa->fresh = dv || one_chunk(X, pa);  // (greedy levels take every cell's child, whatever the bound)
+      if (!pa->fresh) {
+        std::vector<std::pair<uint32_t, uint32_t>> ch;
+        plan_chunks(X, pa, ch);
+        r1 = ch.front().second;
         if (r1 != pa->nkept) carried = false;
       }
       pa->pending = 1;
