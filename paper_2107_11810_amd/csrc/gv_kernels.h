@@ -39,7 +39,7 @@ __device__ inline uint32_t items_of(uint32_t len, uint32_t ilog) { return (len +
 // those of the workgroups before it and writes.  (Large workgroups there
 // waited for sixteen free wave slots of one CU while other lanes' kernels
 // ran: 69 us a k_front on the served problems.)  Totals that the host reads
-// go to host-coherent memory, fenced at system scope.  The device-wide
+// go to host-coherent memory (put_totals).  The device-wide
 // scans, reductions and selections that stood here took 5 to 11 launches an
 // expansion: line2d_10k 1.19 against 1.69 ms, pose5dof_20k 2.73 against 2.96.
 // ---------------------------------------------------------------------------
@@ -93,6 +93,27 @@ __global__ void __launch_bounds__(1024) k_scan_small(const In* __restrict__ in, 
     run += v[j];
   }
   if (total && threadIdx.x == 0) *total = tot;
+}
+
+// Words of a totals block the host polls: t[0..3], then the call's sequence
+// number (unique in the process), visible only after them.
+#define GV_TOT_SEQ 7
+__device__ inline void put_totals(uint64_t* t, uint64_t a, uint64_t b, uint64_t c, uint64_t d, uint64_t seq) {
+  t[0] = a;
+  t[1] = b;
+  t[2] = c;
+  t[3] = d;
+  __threadfence_system();
+  *(volatile uint64_t*)(t + GV_TOT_SEQ) = seq;
+}
+
+// n words of device memory to the staging words behind a totals block
+__global__ void __launch_bounds__(256) k_fetch(const uint32_t* __restrict__ src, uint32_t n, uint32_t* dst, uint64_t* t,
+                                               uint64_t seq) {
+  for (uint32_t i = threadIdx.x; i < n; i += 256u) dst[i] = src[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) *(volatile uint64_t*)(t + GV_TOT_SEQ) = seq;
 }
 
 // sums of one workgroup's elements (n: a count, e: list entries)
@@ -184,7 +205,7 @@ __global__ void __launch_bounds__(1024) k_front(LevelC lv, int B, uint64_t idxma
                                                 const unsigned long long* __restrict__ best, FSum* part,
                                                 uint32_t* __restrict__ order, uint32_t* __restrict__ scount,
                                                 uint32_t* __restrict__ rank_of, uint64_t* __restrict__ soff,
-                                                uint64_t* tot) {
+                                                uint64_t* tot, uint64_t seq) {
   const uint64_t b = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * GV_SMALL_PER;
   uint32_t cnt[GV_SMALL_PER], ent[GV_SMALL_PER], keep = 0;
   uint64_t n = 0, e = 0;
@@ -222,10 +243,7 @@ __global__ void __launch_bounds__(1024) k_front(LevelC lv, int B, uint64_t idxma
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
       soff[upto.n] = upto.e;
-      tot[0] = upto.n;
-      tot[1] = upto.e;
-      tot[2] = best[0];
-      __threadfence_system();
+      put_totals(tot, upto.n, upto.e, best[0], 0, seq);
     }
   }
 }
@@ -237,7 +255,7 @@ __global__ void __launch_bounds__(1024) k_pick(LevelC lv, uint32_t ncell, const 
                                                const uint32_t* __restrict__ cnent, FSum* part,
                                                uint32_t* __restrict__ order, uint32_t* __restrict__ scount,
                                                uint32_t* __restrict__ rank_of, uint64_t* __restrict__ soff,
-                                               uint64_t* tot) {
+                                               uint64_t* tot, uint64_t seq) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x, nch = 1u << lv.abits;
   const uint64_t o = (uint64_t)c << lv.abits;
   uint32_t bc = 0, bd = 0;
@@ -259,10 +277,7 @@ __global__ void __launch_bounds__(1024) k_pick(LevelC lv, uint32_t ncell, const 
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
       soff[ncell] = upto.e;
-      tot[0] = ncell;
-      tot[1] = upto.e;
-      tot[2] = 0;
-      __threadfence_system();
+      put_totals(tot, ncell, upto.e, 0, 0, seq);
     }
   }
 }
@@ -279,7 +294,7 @@ __global__ void __launch_bounds__(1024) k_cut(const uint32_t* __restrict__ keepc
                                               uint64_t* __restrict__ coff, const uint32_t* __restrict__ order,
                                               uint32_t r0, int abits, const uint32_t* __restrict__ ioff,
                                               uint32_t ncell, const uint32_t* __restrict__ nitems_p, int sorted,
-                                              int linear, uint64_t* tot) {
+                                              int linear, uint64_t* tot, uint64_t seq) {
   const uint32_t b = (blockIdx.x * blockDim.x + threadIdx.x) * GV_SMALL_PER;
   uint32_t v[GV_SMALL_PER];
   uint64_t z[GV_SMALL_PER], n = 0, e = 0;
@@ -303,18 +318,13 @@ __global__ void __launch_bounds__(1024) k_cut(const uint32_t* __restrict__ keepc
       e += z[j];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-      tot[0] = upto.n;
-      tot[1] = upto.e;
-      if (linear) {
-        tot[2] = 0;
-        tot[3] = *nitems_p;
-        if (!sorted && nr > 0) {
-          const uint32_t c0 = order[r0] >> abits, c1 = order[r0 + nr - 1] >> abits;
-          tot[2] = ioff[c0];
-          if (c1 + 1 < ncell) tot[3] = ioff[c1 + 1];
-        }
+      uint32_t i0 = 0, i1 = *nitems_p;
+      if (linear && !sorted && nr > 0) {
+        const uint32_t c0 = order[r0] >> abits, c1 = order[r0 + nr - 1] >> abits;
+        i0 = ioff[c0];
+        if (c1 + 1 < ncell) i1 = ioff[c1 + 1];
       }
-      __threadfence_system();
+      put_totals(tot, upto.n, upto.e, i0, i1, seq);
     }
   }
 }
@@ -909,13 +919,11 @@ __global__ void k_prob_norm(const uint32_t* __restrict__ kcnt, const uint32_t* _
 __global__ void k_soff_last(uint64_t* soff, const uint32_t* sn, uint32_t nkept) {
   if (threadIdx.x == 0 && blockIdx.x == 0) soff[nkept] = nkept ? soff[nkept - 1] + sn[nkept - 1] : 0;
 }
-// out may be host-coherent memory the host reads after the stream wait
 __global__ void k_gather_u64(const uint64_t* __restrict__ a, uint64_t n, uint64_t stride, uint64_t* __restrict__ out) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t m = (n + stride - 1) / stride;
   if (i < m) out[i] = a[i * stride];
   if (i == 0) out[m] = a[n];
-  __threadfence_system();
 }
 
 // Re-cut a pending chunk [r0, r1) against the current bounds: a child is
@@ -1482,6 +1490,12 @@ __global__ void k_group_heads(const uint64_t* __restrict__ keys, const uint32_t*
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   head[i] = (i == 0 || keys[i] != keys[i - 1] || !Tuple<E>::same(ents[idx[i]], ents[idx[i - 1]])) ? 1u : 0u;
+}
+
+// number of runs
+__global__ void k_group_total(const uint32_t* __restrict__ head, const uint32_t* __restrict__ hscan, uint64_t n,
+                              uint64_t* tot, uint64_t seq) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) put_totals(tot, (uint64_t)hscan[n - 1] + head[n - 1], 0, 0, 0, seq);
 }
 
 // one thread per run head: the merged entry carries the run's summed weight

@@ -214,10 +214,21 @@ __global__ void k_replay_pose(const ProbC* __restrict__ Ptab, const double* __re
   }
 }
 
-// inliers as indices local to their problem, sorted within each problem
+// bnd[p] = flagged originals before problem p's, bnd[nprob] = all of them
+__global__ void k_inlier_bounds(const uint32_t* __restrict__ flag, const uint32_t* __restrict__ pos,
+                                const uint64_t* __restrict__ ooff, uint32_t nprob, uint64_t Ntot,
+                                uint32_t* __restrict__ bnd) {
+  const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p > nprob) return;
+  const uint64_t o = ooff[p];
+  bnd[p] = o < Ntot ? pos[o] : pos[Ntot - 1] + flag[Ntot - 1];
+}
+
+// inliers as indices local to their problem, sorted within each problem; the
+// first cap of them are written
 __global__ void k_write_inliers(const uint32_t* __restrict__ flag, const uint32_t* __restrict__ pos,
                                 const uint64_t* __restrict__ ooff, uint32_t nprob, uint64_t Ntot,
-                                int64_t* __restrict__ out) {
+                                uint64_t cap, int64_t* __restrict__ out) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < Ntot; i += (uint64_t)gridDim.x * blockDim.x)
-    if (flag[i]) out[pos[i]] = (int64_t)(i - ooff[prob_of(ooff, nprob, i)]);
+    if (flag[i] && pos[i] < cap) out[pos[i]] = (int64_t)(i - ooff[prob_of(ooff, nprob, i)]);
 }

@@ -13,6 +13,7 @@
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -635,6 +636,11 @@ struct Run {
   ProbC P0{};  // level structure shared by the epoch (first problem's constants)
   int group_mode = 0;
   double lat_bound[GV_MAXL + 1];
+  // one device block, uploaded in one copy when the epoch begins (`up` is the
+  // host side, alive until the epoch ends): the problem table, best keys,
+  // counters, offsets and data bounds below
+  void* dstate = nullptr;
+  std::vector<char> up;
   ProbC* dP = nullptr;                    // [nprob]
   unsigned long long* dbest = nullptr;    // [nprob]
   unsigned long long* drecheck = nullptr;
@@ -691,9 +697,12 @@ struct Run {
   uint64_t Ntot = 0;
   std::vector<uint64_t> ooff;             // [nprob + 1]
   uint64_t* dooff = nullptr;
+  int* dbad = nullptr;                    // [nprob] faulty observations seen by the root kernels
+  unsigned long long* dmx = nullptr;      // [8 nprob] data bounds (linear families: 2 unsigned a problem)
   double* m64 = nullptr;                  // POSE4DOF binary64 master, SoA stride Ntot
   void* root = nullptr;                   // root entries (grouped), owned
   Counts counts;                          // count pass of the dive's greedy level, kept for the main search
+  std::vector<Cell> root_lists, root_cells;  // per problem, per (problem, sector): the sources of their uploads
   // search state
   std::vector<Task> stack;
   bool own_first = true;
@@ -703,8 +712,9 @@ struct Run {
 // Two host-coherent pinned words that kernels write totals to, so the host
 // reads them after a stream wait without a copy.  Null pointers (and device
 // memory plus a copy) when the allocation fails.
-// Layout: 8 words of totals, then kStageN + 1 words that the chunk planner's
-// samples are gathered into.
+// Layout: 8 words of totals (the last one a sequence number), then
+// kStageN + 1 words that the chunk planner's samples and small device tables
+// are copied into.
 constexpr uint64_t kStageN = 65536;
 void alloc_hpin(uint64_t*& h, uint64_t*& d) {
   h = d = nullptr;
@@ -826,10 +836,42 @@ void free_counts(Run& X) {
   c = Counts{};
 }
 
-// the first n (<= 4) totals the last kernels wrote to X.dtot
-void read_tot(Run& X, uint64_t* v, int n = 2) {
+// Sequence number of the next totals block: no two in the process are equal,
+// so a block the host reads is the one it waits for.
+uint64_t next_seq() {
+  static std::atomic<uint64_t> n{0};
+  return ++n;
+}
+
+// Waits until a kernel has put `seq` into the host-coherent totals block.
+// Polled first (seen a few microseconds after it is written; a stream wait
+// adds a barrier packet and its cache release), then, for a kernel that runs
+// longer or never writes, the stream wait.  With one upload and polled
+// tables in place of the copies around a solve: line2d_10k 0.71 against
+// 1.11 ms, ray3d_100k 1.23 against 1.61 ms, pose5dof_20k 2.27 against 2.73 ms.
+void wait_seq(Run& X, uint64_t seq) {
+  const volatile uint64_t* f = X.hpin + GV_TOT_SEQ;
+  const auto t0 = std::chrono::steady_clock::now();
+  for (;;) {
+    for (int i = 0; i < 32; i++) {
+      if (*f == seq) {
+        std::atomic_thread_fence(std::memory_order_acquire);
+        X.waits++;
+        X.wait_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+        return;
+      }
+      __builtin_ia32_pause();
+    }
+    if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) break;
+  }
+  host_wait(X);
+}
+
+// the first n (<= 4) totals that the last kernel, given `seq`, wrote to X.dtot
+void read_tot(Run& X, uint64_t* v, int n, uint64_t seq) {
   if (X.hpin && X.dtot == X.hpin_dev) {
-    host_wait(X);
+    HIPCHK(hipGetLastError());
+    wait_seq(X, seq);
     const volatile uint64_t* h = X.hpin;
     for (int i = 0; i < n; i++) v[i] = h[i];
   } else {
@@ -838,11 +880,25 @@ void read_tot(Run& X, uint64_t* v, int n = 2) {
   }
 }
 
+// `bytes` (a multiple of 4) of device memory to the host, waited for
+void fetch(Run& X, void* dst, const void* src, size_t bytes) {
+  if (X.hpin && X.dtot == X.hpin_dev && bytes <= (kStageN + 1) * sizeof(uint64_t)) {
+    const uint64_t seq = next_seq();
+    k_fetch<<<1, 256, 0, X.st>>>((const uint32_t*)src, (uint32_t)(bytes / 4), (uint32_t*)(X.hpin_dev + 8), X.hpin_dev,
+                                 seq);
+    HIPCHK(hipGetLastError());
+    wait_seq(X, seq);
+    std::memcpy(dst, X.hpin + 8, bytes);
+  } else {
+    HIPCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, X.st));
+    host_wait(X);
+  }
+}
+
 template <typename T>
 uint64_t d2h1(Run& X, const T* p) {
   T v{};
-  HIPCHK(hipMemcpyAsync(&v, p, sizeof(T), hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
+  fetch(X, &v, p, sizeof(T));
   return (uint64_t)v;
 }
 
@@ -1015,11 +1071,10 @@ void group_batch(Run& X, Batch& b, bool own_ents) {
   uint32_t* hscan = dalloc<uint32_t>(X, n);
   k_group_heads<E><<<nblk(n), 256, 0, X.st>>>(k1, i1, (const E*)b.ents, n, head);
   excl_scan(X, head, hscan, n);
-  uint32_t last[2];
-  HIPCHK(hipMemcpyAsync(&last[0], hscan + n - 1, 4, hipMemcpyDeviceToHost, X.st));
-  HIPCHK(hipMemcpyAsync(&last[1], head + n - 1, 4, hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
-  const uint64_t U = (uint64_t)last[0] + last[1];
+  uint64_t U = 0;
+  const uint64_t seq = next_seq();
+  k_group_total<<<1, 64, 0, X.st>>>(head, hscan, n, X.dtot, seq);
+  read_tot(X, &U, 1, seq);
   if (U < n) {
     E* out = dalloc<E>(X, U);
     k_group_write<E><<<nblk(n), 256, 0, X.st>>>(i1, (const E*)b.ents, n, head, hscan, out);
@@ -1311,17 +1366,18 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
   const unsigned per = dive ? 1u : (unsigned)GV_SMALL_PER;
   const unsigned wg = nsel <= 1024u * per ? 1024u : GV_FRONT_WG, g = nblk(nsel, wg * per);
   FSum* part = g > 1 ? dalloc<FSum>(X, g) : nullptr;
+  const uint64_t seq = next_seq();
   if (dive) {
 #define GV_PICK(W)                                                                                              \
   k_pick<W><<<g, wg, 0, X.st>>>(lv, b.ncell, ccnt, pa->cnent, part, pa->order, pa->scount, pa->rank_of, pa->soff, \
-                                  X.dtot)
+                                  X.dtot, seq)
     if (g > 1) GV_PICK(false);
     GV_PICK(true);
 #undef GV_PICK
   } else {
 #define GV_FRONT(W)                                                                                              \
   k_front<W><<<g, wg, 0, X.st>>>(lv, P.B, P.idxmask, b.cells, nk, ccnt, pa->cnent, X.dbest, part, pa->order,     \
-                                   pa->scount, pa->rank_of, pa->soff, X.dtot)
+                                   pa->scount, pa->rank_of, pa->soff, X.dtot, seq)
     if (g > 1) GV_FRONT(false);
     GV_FRONT(true);
 #undef GV_FRONT
@@ -1333,7 +1389,7 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
     X.counts = Counts{true, pa->items, pa->nitems, pa->max_items, pa->ioff, pa->itemoff, pa->masks, ccnt, pa->cnent};
   }
   uint64_t kt[3];
-  read_tot(X, kt, 3);
+  read_tot(X, kt, 3, seq);
   pa->nkept = (uint32_t)kt[0];
   pa->kept_entries = kt[1];
   pa->best = kt[2];
@@ -1369,18 +1425,10 @@ void plan_chunks(Run& X, Parent* pa, std::vector<std::pair<uint32_t, uint32_t>>&
   const uint64_t stride = std::max<uint64_t>(1, ((uint64_t)nk + kStageN - 1) / kStageN);
   const uint64_t ns = (nk + stride - 1) / stride;  // samples soff[i*stride], plus soff[nk]
   std::vector<uint64_t> s(ns + 1);
-  if (X.hpin) {
-    // gathered straight into host-coherent memory: no copy
-    k_gather_u64<<<nblk(ns + 1), 256, 0, X.st>>>(pa->soff, nk, stride, X.hpin_dev + 8);
-    host_wait(X);
-    std::memcpy(s.data(), X.hpin + 8, (ns + 1) * sizeof(uint64_t));
-  } else {
-    uint64_t* d = dalloc<uint64_t>(X, ns + 1);
-    k_gather_u64<<<nblk(ns + 1), 256, 0, X.st>>>(pa->soff, nk, stride, d);
-    HIPCHK(hipMemcpyAsync(s.data(), d, (ns + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, X.st));
-    host_wait(X);
-    dfree(X, d);
-  }
+  uint64_t* d = dalloc<uint64_t>(X, ns + 1);
+  k_gather_u64<<<nblk(ns + 1), 256, 0, X.st>>>(pa->soff, nk, stride, d);
+  fetch(X, s.data(), d, (ns + 1) * sizeof(uint64_t));
+  dfree(X, d);
   auto at = [&](uint64_t i) { return i >= ns ? s[ns] : s[i]; };  // sample i -> soff[min(i*stride, nk)]
   auto rk = [&](uint64_t i) { return (uint32_t)std::min<uint64_t>(i * stride, nk); };
   const int lc = std::min(pa->level + 1, X.P0.Lstar - 1);
@@ -1483,15 +1531,16 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
     }
     const unsigned wg = nr <= GV_SMALL_N ? 1024u : GV_FRONT_WG, g = nblk(nr, wg * GV_SMALL_PER);
     FSum* part = g > 1 ? dalloc<FSum>(X, g) : nullptr;
+    const uint64_t seq = next_seq();
 #define GV_CUT(W)                                                                                               \
   k_cut<W><<<g, wg, 0, X.st>>>(keepc, csize, nr, part, cidx, coff, pa->order, r0, lv.abits, pa->ioff, pa->ncell, \
-                                 pa->nitems, pa->sorted ? 1 : 0, linear ? 1 : 0, X.dtot)
+                                 pa->nitems, pa->sorted ? 1 : 0, linear ? 1 : 0, X.dtot, seq)
     if (g > 1) GV_CUT(false);
     GV_CUT(true);
 #undef GV_CUT
     HIPCHK(hipGetLastError());
     dfree(X, part);
-    read_tot(X, tot, linear ? 4 : 2);
+    read_tot(X, tot, linear ? 4 : 2, seq);
   }
   bool made = false;
   X.stats.cells_pruned += nr - tot[0];
@@ -1750,35 +1799,43 @@ void epoch_begin(Run& X) {
   if (const char* e = std::getenv("GV_REUSE")) X.reuse = atoi(e) != 0;
   if (const char* rd = std::getenv("GV_ROOT_DIVE")) X.root_dive = atoi(rd) != 0;
   HIPCHK(hipSetDevice(X.ctx->device));
-  X.dP = dalloc<ProbC>(X, np);
-  X.dbest = dalloc<unsigned long long>(X, np);
-  X.drecheck = dalloc<unsigned long long>(X, 1);
-  X.dtests = dalloc<unsigned long long>(X, 2);
-  HIPCHK(hipMemsetAsync(X.dtests, 0, 16, X.st));
+  // the epoch's device block (see Run::dstate)
+  {
+    size_t o = 0;
+    auto put = [&](size_t bytes) {
+      const size_t at = o;
+      o += (bytes + 15) & ~(size_t)15;
+      return at;
+    };
+    const size_t oP = put(np * sizeof(ProbC)), oOff = put((np + 1) * 8), oBest = put(np * 8), oCtr = put(5 * 8),
+                 oBad = put(np * sizeof(int)), oMx = put(8 * np * 8);
+    X.up.assign(o, 0);
+    for (uint32_t p = 0; p < np; p++) {
+      std::memcpy(X.up.data() + oP + p * sizeof(ProbC), &X.probs[p]->S.P, sizeof(ProbC));
+      // (reporting: every problem's key stays at its threshold)
+      const unsigned long long b0 = X.report ? (unsigned long long)((X.tau << X.probs[p]->S.P.B) - 1ull) : 0ull;
+      std::memcpy(X.up.data() + oBest + p * 8, &b0, 8);
+    }
+    std::memcpy(X.up.data() + oOff, X.ooff.data(), (np + 1) * 8);
+    X.dstate = dalloc<char>(X, o);
+    char* d = (char*)X.dstate;
+    X.dP = (ProbC*)(d + oP);
+    X.dooff = (uint64_t*)(d + oOff);
+    X.dbest = (unsigned long long*)(d + oBest);
+    X.dtests = (unsigned long long*)(d + oCtr);  // two words
+    X.drecheck = X.dtests + 2;
+    X.dreads = X.dtests + 3;
+    X.dovf = (int*)(X.dtests + 4);
+    X.dbad = (int*)(d + oBad);
+    X.dmx = (unsigned long long*)(d + oMx);
+    HIPCHK(hipMemcpyAsync(X.dstate, X.up.data(), o, hipMemcpyHostToDevice, X.st));
+  }
   if (const char* e = std::getenv("GV_PROBE")) X.probe = atoi(e);
   if (const char* e = std::getenv("GV_SUBTREE")) X.subtree = atoi(e) != 0;
   if (const char* e = std::getenv("GV_SUBTREE_FROM")) X.subtree_from = atoi(e);
   if (X.subtree_from < 0) X.subtree_from = std::max(1, X.P0.Lstar + X.subtree_from);
-  X.dtot = X.hpin_dev ? X.hpin_dev : dalloc<uint64_t>(X, 4);
-  X.dreads = dalloc<unsigned long long>(X, 1);
-  X.dovf = dalloc<int>(X, 1);
+  X.dtot = X.hpin_dev ? X.hpin_dev : dalloc<uint64_t>(X, 8);
   X.pack_from = 1 << 30;
-  X.dooff = dalloc<uint64_t>(X, np + 1);
-  if (X.report) {
-    std::vector<unsigned long long> b0(np);
-    for (uint32_t p = 0; p < np; p++) b0[p] = (unsigned long long)((X.tau << X.probs[p]->S.P.B) - 1ull);
-    HIPCHK(hipMemcpyAsync(X.dbest, b0.data(), np * 8, hipMemcpyHostToDevice, X.st));
-    host_wait(X);
-  } else {
-    HIPCHK(hipMemsetAsync(X.dbest, 0, np * 8, X.st));
-  }
-  HIPCHK(hipMemsetAsync(X.drecheck, 0, 8, X.st));
-  HIPCHK(hipMemsetAsync(X.dreads, 0, 8, X.st));
-  HIPCHK(hipMemsetAsync(X.dovf, 0, sizeof(int), X.st));
-  HIPCHK(hipMemcpyAsync(X.dooff, X.ooff.data(), (np + 1) * 8, hipMemcpyHostToDevice, X.st));
-  std::vector<ProbC> tab(np);
-  for (uint32_t p = 0; p < np; p++) tab[p] = X.probs[p]->S.P;
-  HIPCHK(hipMemcpyAsync(X.dP, tab.data(), np * sizeof(ProbC), hipMemcpyHostToDevice, X.st));
   for (ProbRec* pr : X.probs) {
     const int nc = ncols_of(pr->S.fam, pr->S.d);
     for (int k = 0; k < nc; k++) {
@@ -1792,7 +1849,6 @@ void epoch_begin(Run& X) {
       }
     }
   }
-  host_wait(X);  // tables and copied columns are read below
 }
 
 // Root cells of every valid problem, grouping of equal root surfaces, one
@@ -1803,7 +1859,8 @@ void start_search(Run& X) {
   X.ent_bytes = sizeof(E) + sizeof(M);
   const uint32_t np = (uint32_t)X.probs.size();
   const int nsec = P.nsec;
-  std::vector<Cell> rc;
+  std::vector<Cell>& rc = X.root_lists;
+  rc.clear();
   for (uint32_t p = 0; p < np; p++) {
     if (X.probs[p]->st != GV_OK) continue;
     Cell c{};
@@ -1820,18 +1877,21 @@ void start_search(Run& X) {
     rb.ncell = (uint32_t)rc.size();
     rb.nent = X.Ntot;
     rb.cells = dalloc<Cell>(X, rc.size());
-    // (rc stays alive and is next written by a copy later on the same stream)
-    HIPCHK(hipMemcpyAsync(rb.cells, rc.data(), rc.size() * sizeof(Cell), hipMemcpyHostToDevice, X.st));
-    rb.ents = X.root;
-    if (X.group_mode >= 0) group_batch<E>(X, rb, true);
-    X.root = rb.ents;
-    unit = rb.unit;
-    HIPCHK(hipMemcpyAsync(rc.data(), rb.cells, rc.size() * sizeof(Cell), hipMemcpyDeviceToHost, X.st));
-    host_wait(X);
+    if (X.group_mode >= 0) {
+      HIPCHK(hipMemcpyAsync(rb.cells, rc.data(), rc.size() * sizeof(Cell), hipMemcpyHostToDevice, X.st));
+      rb.ents = X.root;
+      group_batch<E>(X, rb, true);
+      X.root = rb.ents;
+      unit = rb.unit;
+      // (merged lists, after group_batch's wait: one list is all there is)
+      if (!unit && rc.size() == 1) rc[0].len = (uint32_t)rb.nent;
+      else if (!unit) fetch(X, rc.data(), rb.cells, rc.size() * sizeof(Cell));
+    }
     dfree(X, rb.cells);
   }
   // one list per (problem, sector): the pass masks are written per entry
-  std::vector<Cell> cells;
+  std::vector<Cell>& cells = X.root_cells;
+  cells.clear();
   uint64_t tot = 0;
   for (const Cell& c : rc)
     for (int s = 0; s < nsec; s++) {
@@ -1854,9 +1914,11 @@ void start_search(Run& X) {
     dfree(X, X.root);
   }
   X.root = nullptr;
-  Cell* dcells = dalloc<Cell>(X, cells.size());
-  HIPCHK(hipMemcpyAsync(dcells, cells.data(), cells.size() * sizeof(Cell), hipMemcpyHostToDevice, X.st));
-  host_wait(X);
+  auto upload_cells = [&]() {
+    Cell* d = dalloc<Cell>(X, cells.size());
+    HIPCHK(hipMemcpyAsync(d, cells.data(), cells.size() * sizeof(Cell), hipMemcpyHostToDevice, X.st));
+    return d;
+  };
   // greedy dive in every cell: achieved leaf keys are valid starting bounds
   if (X.root_dive && !X.report) {
     Batch b;
@@ -1864,8 +1926,7 @@ void start_search(Run& X) {
     b.ncell = (uint32_t)cells.size();
     b.nent = tot;
     b.unit = unit;
-    b.cells = dalloc<Cell>(X, cells.size());
-    HIPCHK(hipMemcpyAsync(b.cells, dcells, cells.size() * sizeof(Cell), hipMemcpyDeviceToDevice, X.st));
+    b.cells = upload_cells();
     b.ents = ents;
     bool own = false;
     while (true) {
@@ -1901,8 +1962,7 @@ void start_search(Run& X) {
     b.ncell = (uint32_t)cells.size();
     b.nent = tot;
     b.unit = unit;
-    b.cells = dalloc<Cell>(X, cells.size());
-    HIPCHK(hipMemcpyAsync(b.cells, dcells, cells.size() * sizeof(Cell), hipMemcpyDeviceToDevice, X.st));
+    b.cells = upload_cells();
     b.ents = ents;
     bool own = false;
     bool carried = X.reuse && !X.root_dive && !X.fixed;
@@ -1938,14 +1998,13 @@ void start_search(Run& X) {
   t.chunk = false;
   if (have_reuse) {
     t.b = reuse;
-    dfree(X, dcells);
     dfree(X, ents);
   } else {
     t.b.level = 0;
     t.b.ncell = (uint32_t)cells.size();
     t.b.nent = tot;
     t.b.unit = unit;
-    t.b.cells = dcells;
+    t.b.cells = upload_cells();
     t.b.ents = ents;
   }
   X.stack.push_back(t);
@@ -1975,8 +2034,7 @@ void run_subtree(Run& X, Batch& b) {
                                                      mbuf, nframes);
   HIPCHK(hipGetLastError());
   uint32_t back[2] = {0, 0};
-  HIPCHK(hipMemcpyAsync(back, ctr + 1, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
+  fetch(X, back, ctr + 1, 2 * sizeof(uint32_t));
   dfree(X, fbuf);
   dfree(X, mbuf);
   dfree(X, ctr);
@@ -2036,28 +2094,31 @@ bool epoch_step(Run& X) {
   return !X.stack.empty();
 }
 
+// the root kernels' flags and data bounds (mx: the first mx_bytes of X.dmx,
+// which follows X.dbad in the epoch's device block)
+void fetch_bounds(Run& X, std::vector<int>& bad, void* mx, size_t mx_bytes) {
+  const size_t lead = (size_t)((const char*)X.dmx - (const char*)X.dbad);
+  std::vector<char> h(lead + mx_bytes);
+  fetch(X, h.data(), X.dbad, h.size());
+  std::memcpy(bad.data(), h.data(), bad.size() * sizeof(int));
+  if (mx_bytes) std::memcpy(mx, h.data() + lead, mx_bytes);
+}
+
 template <int FAM>
 void build_linear(Run& X) {
   using E = typename EntOf<FAM>::T;
   const uint32_t np = (uint32_t)X.probs.size();
   E* root = dalloc<E>(X, X.Ntot);
-  unsigned* dmax = dalloc<unsigned>(X, 2 * np);
-  int* dbad = dalloc<int>(X, np);
-  HIPCHK(hipMemsetAsync(dmax, 0, 2 * np * sizeof(unsigned), X.st));
-  HIPCHK(hipMemsetAsync(dbad, 0, np * sizeof(int), X.st));
+  unsigned* dmax = (unsigned*)X.dmx;
   for (uint32_t p = 0; p < np; p++) {
     ProbRec* pr = X.probs[p];
     if (pr->n > 0)
       k_root_lin<FAM><<<gs_grid(X, pr->n), 256, 0, X.st>>>(X.dP + p, pr->cols, pr->n, root + X.ooff[p], dmax + 2 * p,
-                                                           dbad + p);
+                                                           X.dbad + p);
   }
   std::vector<unsigned> mx(2 * np);
   std::vector<int> bad(np);
-  HIPCHK(hipMemcpyAsync(mx.data(), dmax, 2 * np * sizeof(unsigned), hipMemcpyDeviceToHost, X.st));
-  HIPCHK(hipMemcpyAsync(bad.data(), dbad, np * sizeof(int), hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
-  dfree(X, dmax);
-  dfree(X, dbad);
+  fetch_bounds(X, bad, mx.data(), mx.size() * sizeof(unsigned));
   const ProbC& P = X.P0;
   double Hmax = 0, padmax = 0;
   for (int j = 0; j < X.probs[0]->S.d; j++) {
@@ -2161,17 +2222,13 @@ template <int BF>
 void build_exact(Run& X) {
   const uint32_t np = (uint32_t)X.probs.size();
   EntX* root = dalloc<EntX>(X, X.Ntot);
-  int* dbad = dalloc<int>(X, np);
-  HIPCHK(hipMemsetAsync(dbad, 0, np * sizeof(int), X.st));
   for (uint32_t p = 0; p < np; p++) {
     ProbRec* pr = X.probs[p];
     if (pr->n > 0)
-      k_root_x<BF><<<gs_grid(X, pr->n), 256, 0, X.st>>>(X.dP + p, pr->cols, pr->n, root + X.ooff[p], dbad + p);
+      k_root_x<BF><<<gs_grid(X, pr->n), 256, 0, X.st>>>(X.dP + p, pr->cols, pr->n, root + X.ooff[p], X.dbad + p);
   }
   std::vector<int> bad(np);
-  HIPCHK(hipMemcpyAsync(bad.data(), dbad, np * sizeof(int), hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
-  dfree(X, dbad);
+  fetch_bounds(X, bad, nullptr, 0);
   for (uint32_t p = 0; p < np; p++) {
     ProbRec* pr = X.probs[p];
     if (bad[p] & 1) {
@@ -2196,21 +2253,15 @@ bool step_pose5(Run& X) { return epoch_step<FAM_POSE5DOF, E, uint32_t>(X); }
 // returns true when the binary32 filter is used
 bool build_pose(Run& X) {
   const uint32_t np = (uint32_t)X.probs.size();
-  unsigned long long* dmx = dalloc<unsigned long long>(X, 8 * np);
-  int* dbad = dalloc<int>(X, np);
-  HIPCHK(hipMemsetAsync(dmx, 0, 8 * np * sizeof(unsigned long long), X.st));
-  HIPCHK(hipMemsetAsync(dbad, 0, np * sizeof(int), X.st));
+  unsigned long long* dmx = X.dmx;
   for (uint32_t p = 0; p < np; p++) {
     ProbRec* pr = X.probs[p];
     if (pr->n > 0)
-      k_pose_bounds<<<gs_grid(X, pr->n), 256, 0, X.st>>>(X.dP + p, X.fam, pr->cols, pr->n, dmx + 8 * p, dbad + p);
+      k_pose_bounds<<<gs_grid(X, pr->n), 256, 0, X.st>>>(X.dP + p, X.fam, pr->cols, pr->n, dmx + 8 * p, X.dbad + p);
   }
   std::vector<unsigned long long> mxb(8 * np);
   std::vector<int> bad(np);
-  HIPCHK(hipMemcpyAsync(mxb.data(), dmx, mxb.size() * 8, hipMemcpyDeviceToHost, X.st));
-  HIPCHK(hipMemcpyAsync(bad.data(), dbad, np * sizeof(int), hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
-  std::vector<ProbC> tab(np);
+  fetch_bounds(X, bad, mxb.data(), mxb.size() * 8);
   for (uint32_t p = 0; p < np; p++) {
     ProbRec* pr = X.probs[p];
     double H, R2, Xm;
@@ -2226,10 +2277,10 @@ bool build_pose(Run& X) {
       pr->err = "POSE5DOF: image coordinates times the f range too wide (2 atan(1 + 2 eps[3]) + atan(max|xi| hi[4]) "
                 "must stay below 3.1)";
     }
-    tab[p] = pr->S.P;
+    std::memcpy(X.up.data() + p * sizeof(ProbC), &pr->S.P, sizeof(ProbC));
   }
   X.P0 = X.probs[0]->S.P;
-  HIPCHK(hipMemcpyAsync(X.dP, tab.data(), np * sizeof(ProbC), hipMemcpyHostToDevice, X.st));
+  HIPCHK(hipMemcpyAsync(X.dP, X.up.data(), np * sizeof(ProbC), hipMemcpyHostToDevice, X.st));
   X.m64 = dalloc<double>(X, X.Ntot * 5);
   EntQ32* e32 = dalloc<EntQ32>(X, X.Ntot);
   EntQ64* e64 = dalloc<EntQ64>(X, X.Ntot);
@@ -2239,10 +2290,7 @@ bool build_pose(Run& X) {
       k_root_pose<<<gs_grid(X, pr->n), 256, 0, X.st>>>(X.dP + p, X.fam, pr->cols, pr->n, X.ooff[p], X.Ntot, X.m64,
                                                        e32, e64, dmx + 8 * p);
   }
-  HIPCHK(hipMemcpyAsync(mxb.data(), dmx, mxb.size() * 8, hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
-  dfree(X, dmx);
-  dfree(X, dbad);
+  fetch_bounds(X, bad, mxb.data(), mxb.size() * 8);
   bool all32 = true;
   for (uint32_t p = 0; p < np; p++) {
     ProbRec* pr = X.probs[p];
@@ -2282,40 +2330,46 @@ bool build_pose(Run& X) {
 void epoch_finish(Run& X) {
   const uint32_t np = (uint32_t)X.probs.size();
   const ProbC& P = X.P0;
+  // the best keys and the counters behind them in the epoch's device block
+  const size_t lead = (size_t)((const char*)X.dtests - (const char*)X.dbest);
+  std::vector<char> h(lead + 5 * 8);
+  fetch(X, h.data(), X.dbest, h.size());
   std::vector<unsigned long long> best(np);
-  unsigned long long rech = 0;
+  std::memcpy(best.data(), h.data(), np * 8);
+  unsigned long long ctr[5];
+  std::memcpy(ctr, h.data() + lead, sizeof(ctr));
   int ovf = 0;
-  HIPCHK(hipMemcpyAsync(best.data(), X.dbest, np * 8, hipMemcpyDeviceToHost, X.st));
-  HIPCHK(hipMemcpyAsync(&rech, X.drecheck, 8, hipMemcpyDeviceToHost, X.st));
-  HIPCHK(hipMemcpyAsync(&ovf, X.dovf, sizeof(int), hipMemcpyDeviceToHost, X.st));
-  host_wait(X);
+  std::memcpy(&ovf, &ctr[4], sizeof(int));
   if (ovf)
     for (ProbRec* pr : X.probs)
       if (pr->st == GV_OK) {
         pr->st = GV_ERANGE;
         pr->err = "internal: a lattice value outgrew its packed list entry";
       }
-  std::vector<PathC> paths(np);
-  std::vector<Cols> ctab(np);
+  // columns and paths of every problem, uploaded in one copy
+  std::vector<char> tab(np * (sizeof(Cols) + sizeof(PathC)));
+  bool all_ok = true;
+  uint64_t tot = 0;
   for (uint32_t p = 0; p < np; p++) {
     ProbRec* pr = X.probs[p];
-    ctab[p] = pr->cols;
     pr->count = best[p] >> P.B;
     pr->leaf = P.idxmask - (best[p] & P.idxmask);
     decode_leaf(P, pr->leaf, pr->path, pr->coords);
-    paths[p] = pr->path;
+    std::memcpy(tab.data() + p * sizeof(Cols), &pr->cols, sizeof(Cols));
+    std::memcpy(tab.data() + np * sizeof(Cols) + p * sizeof(PathC), &pr->path, sizeof(PathC));
+    all_ok = all_ok && pr->st == GV_OK;
+    tot += pr->count;
   }
-  PathC* dpaths = dalloc<PathC>(X, np);
-  Cols* dctab = dalloc<Cols>(X, np);
-  HIPCHK(hipMemcpyAsync(dpaths, paths.data(), np * sizeof(PathC), hipMemcpyHostToDevice, X.st));
-  HIPCHK(hipMemcpyAsync(dctab, ctab.data(), np * sizeof(Cols), hipMemcpyHostToDevice, X.st));
-  std::vector<uint64_t> bnd(np + 1, 0);
+  char* dtab = dalloc<char>(X, tab.size());
+  const Cols* dctab = (const Cols*)dtab;
+  const PathC* dpaths = (const PathC*)(dtab + np * sizeof(Cols));
+  HIPCHK(hipMemcpyAsync(dtab, tab.data(), tab.size(), hipMemcpyHostToDevice, X.st));
+  std::vector<uint32_t> bnd(np + 1, 0);
   std::vector<int64_t> all;
   if (X.Ntot > 0) {
     uint32_t* flag = dalloc<uint32_t>(X, X.Ntot);
     uint32_t* pos = dalloc<uint32_t>(X, X.Ntot + 1);
-    int* dbad = dalloc<int>(X, 1);
-    HIPCHK(hipMemsetAsync(dbad, 0, sizeof(int), X.st));
+    int* dbad = X.dbad;  // (faulty observations were reported when the roots were built)
     const unsigned gg = gs_grid(X, X.Ntot);
     if (X.P0.exact && !fam_pose(X.fam)) {
       switch (X.fam) {
@@ -2334,30 +2388,28 @@ void epoch_finish(Run& X) {
     }
     HIPCHK(hipGetLastError());
     excl_scan(X, flag, pos, X.Ntot);
-    uint32_t lastf = 0;
-    HIPCHK(hipMemcpyAsync(&lastf, flag + X.Ntot - 1, 4, hipMemcpyDeviceToHost, X.st));
-    std::vector<uint32_t> pb(np + 1);
-    for (uint32_t p = 0; p < np; p++)
-      HIPCHK(hipMemcpyAsync(&pb[p], pos + std::min<uint64_t>(X.ooff[p], X.Ntot - 1), 4, hipMemcpyDeviceToHost, X.st));
-    HIPCHK(hipMemcpyAsync(&pb[np], pos + X.Ntot - 1, 4, hipMemcpyDeviceToHost, X.st));
-    host_wait(X);
-    pb[np] += lastf;
-    for (uint32_t p = 0; p < np; p++)
-      if (X.ooff[p] >= X.Ntot) pb[p] = pb[np];
-    for (uint32_t p = 0; p <= np; p++) bnd[p] = pb[p];
-    const uint64_t tot = bnd[np];
-    if (tot > 0) {
-      int64_t* dout = dalloc<int64_t>(X, tot);
-      k_write_inliers<<<gg, 256, 0, X.st>>>(flag, pos, X.dooff, np, X.Ntot, dout);
-      all.resize(tot);
-      HIPCHK(hipMemcpyAsync(all.data(), dout, tot * sizeof(int64_t), hipMemcpyDeviceToHost, X.st));
-      host_wait(X);
-      dfree(X, dout);
+    uint32_t* dbnd = dalloc<uint32_t>(X, np + 1);
+    k_inlier_bounds<<<nblk(np + 1), 256, 0, X.st>>>(flag, pos, X.dooff, np, X.Ntot, dbnd);
+    // The replayed inliers must number the leaves' counts, so that many are
+    // written and copied without waiting for their number, which is checked
+    // below.  (A failed problem's path says nothing: then the number first.)
+    if (!all_ok) {
+      fetch(X, bnd.data(), dbnd, (np + 1) * sizeof(uint32_t));
+      tot = bnd[np];
     }
+    tot = std::min<uint64_t>(tot, X.Ntot);
+    int64_t* dout = dalloc<int64_t>(X, tot);
+    k_write_inliers<<<gg, 256, 0, X.st>>>(flag, pos, X.dooff, np, X.Ntot, tot, dout);
+    HIPCHK(hipGetLastError());
+    all.resize(tot);
+    if (tot) HIPCHK(hipMemcpyAsync(all.data(), dout, tot * sizeof(int64_t), hipMemcpyDeviceToHost, X.st));
+    if (all_ok) fetch(X, bnd.data(), dbnd, (np + 1) * sizeof(uint32_t));
+    dfree(X, dbnd);
+    dfree(X, dout);
     dfree(X, flag);
     dfree(X, pos);
-    dfree(X, dbad);
   }
+  host_wait(X);  // (the inliers' copy, and the events below)
   // kernel timing
   for (auto& e : X.ev) {
     float ms = 0.f;
@@ -2366,10 +2418,12 @@ void epoch_finish(Run& X) {
     if (e.cand >= 0) tune_sample(X, e.kind, e.cand, (double)ms, e.units);
     if (e.tcand >= 0) tune_sample(X, 2, e.tcand, (double)ms, e.units);
   }
-  if (X.ctx->kernel_timing) X.stats.compact_bytes += d2h1(X, X.dreads) / 8;
-  X.stats.fp64_rechecks = rech;
-  X.stats.tests += d2h1(X, X.dtests);
-  if (X.ctx->kernel_timing) X.stats.test_bytes += d2h1(X, X.dtests + 1);
+  X.stats.fp64_rechecks = ctr[2];
+  X.stats.tests += ctr[0];
+  if (X.ctx->kernel_timing) {
+    X.stats.test_bytes += ctr[1];
+    X.stats.compact_bytes += ctr[3] / 8;
+  }
   X.stats.levels = (uint32_t)P.Lstar;
   const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - X.t0).count();
   X.stats.ms_total = ms;
@@ -2384,14 +2438,14 @@ void epoch_finish(Run& X) {
     ProbRec* pr = X.probs[p];
     pr->stats = X.stats;
     if (pr->st != GV_OK) continue;
-    pr->inliers.assign(all.begin() + (int64_t)bnd[p], all.begin() + (int64_t)bnd[p + 1]);
-    if ((uint64_t)pr->inliers.size() != pr->count) {
+    if ((uint64_t)bnd[p + 1] - bnd[p] != pr->count || bnd[p + 1] > all.size()) {
       pr->st = GV_EDEVICE;
       pr->err = "internal: replayed inlier count differs from the leaf count";
+      continue;
     }
+    pr->inliers.assign(all.begin() + (int64_t)bnd[p], all.begin() + (int64_t)bnd[p + 1]);
   }
-  dfree(X, dpaths);
-  dfree(X, dctab);
+  dfree(X, dtab);
 }
 
 // free everything an epoch may still hold (also after an error)
@@ -2416,22 +2470,10 @@ void epoch_release(Run& X) {
     for (void* q : pr->dev_owned) dfree(X, q);
     pr->dev_owned.clear();
   }
-  dfree(X, X.dP);
-  dfree(X, X.dbest);
-  dfree(X, X.drecheck);
-  dfree(X, X.dtests);
-  X.dtests = nullptr;
   if (X.dtot != X.hpin_dev) dfree(X, X.dtot);
-  dfree(X, X.dreads);
-  dfree(X, X.dovf);
-  dfree(X, X.dooff);
-  X.dP = nullptr;
-  X.dbest = nullptr;
-  X.drecheck = nullptr;
   X.dtot = nullptr;
-  X.dreads = nullptr;
-  X.dovf = nullptr;
-  X.dooff = nullptr;
+  dfree(X, X.dstate);
+  X.dstate = nullptr;
 }
 
 // build an epoch and return its step function
@@ -2869,10 +2911,9 @@ gv_status gv_report(gv_ctx* ctx, const gv_problem* p, uint64_t tau, uint64_t* le
       auto step = epoch_build(X);
       while (step(X)) {
       }
-      unsigned long long nn = 0;
-      HIPCHK(hipMemcpyAsync(&nn, X.rep_n, 8, hipMemcpyDeviceToHost, X.st));
-      host_wait(X);
+      const uint64_t nn = d2h1(X, X.rep_n);
       total = nn;
+      X.stats.tests += d2h1(X, X.dtests);
       const uint64_t k = std::min<uint64_t>(nn, cap);
       if (k > 0) {
         std::vector<uint64_t> hi(k);
