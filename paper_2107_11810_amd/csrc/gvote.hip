@@ -703,6 +703,7 @@ struct Run {
   void* root = nullptr;                   // root entries (grouped), owned
   Counts counts;                          // count pass of the dive's greedy level, kept for the main search
   std::vector<Cell> root_lists, root_cells;  // per problem, per (problem, sector): the sources of their uploads
+  bool idle = false;  // everything enqueued is known to have ended
   // search state
   std::vector<Task> stack;
   bool own_first = true;
@@ -751,6 +752,7 @@ void bind_ctx(Run& X, gv_ctx* c) {
   X.ev_pool = &c->ev_pool;
   X.hpin = c->hpin;
   X.hpin_dev = c->hpin_dev;
+  X.dtot = c->hpin_dev;
   X.err = &c->err;
   X.budget = c->budget;
 }
@@ -880,7 +882,10 @@ void read_tot(Run& X, uint64_t* v, int n, uint64_t seq) {
   }
 }
 
-// `bytes` (a multiple of 4) of device memory to the host, waited for
+// `bytes` (a multiple of 4) of device memory to the host, waited for.  Tables
+// beyond kFetchBytes that may be larger (inliers) go by a copy instead: one
+// workgroup writes them to the host, about 5 GB/s.
+constexpr size_t kFetchBytes = 64u << 10;
 void fetch(Run& X, void* dst, const void* src, size_t bytes) {
   if (X.hpin && X.dtot == X.hpin_dev && bytes <= (kStageN + 1) * sizeof(uint64_t)) {
     const uint64_t seq = next_seq();
@@ -2402,14 +2407,20 @@ void epoch_finish(Run& X) {
     k_write_inliers<<<gg, 256, 0, X.st>>>(flag, pos, X.dooff, np, X.Ntot, tot, dout);
     HIPCHK(hipGetLastError());
     all.resize(tot);
-    if (tot) HIPCHK(hipMemcpyAsync(all.data(), dout, tot * sizeof(int64_t), hipMemcpyDeviceToHost, X.st));
+    if (tot * sizeof(int64_t) <= kFetchBytes) {
+      if (tot) fetch(X, all.data(), dout, tot * sizeof(int64_t));
+    } else {
+      HIPCHK(hipMemcpyAsync(all.data(), dout, tot * sizeof(int64_t), hipMemcpyDeviceToHost, X.st));
+      host_wait(X);
+    }
     if (all_ok) fetch(X, bnd.data(), dbnd, (np + 1) * sizeof(uint32_t));
     dfree(X, dbnd);
     dfree(X, dout);
     dfree(X, flag);
     dfree(X, pos);
   }
-  host_wait(X);  // (the inliers' copy, and the events below)
+  if (!X.ev.empty()) host_wait(X);
+  X.idle = true;
   // kernel timing
   for (auto& e : X.ev) {
     float ms = 0.f;
@@ -2450,7 +2461,7 @@ void epoch_finish(Run& X) {
 
 // free everything an epoch may still hold (also after an error)
 void epoch_release(Run& X) {
-  (void)hipStreamSynchronize(X.st);
+  if (!X.idle) (void)hipStreamSynchronize(X.st);
   while (!X.stack.empty()) {
     Task t = X.stack.back();
     X.stack.pop_back();
@@ -3363,47 +3374,41 @@ gv_status gv_refine(gv_ctx* ctx, const gv_problem* p, uint64_t leaf_index, const
     RefState* dS = dalloc<RefState>(X, 2);  // [0]: the pose; [1]: the first sums, at the leaf centre
     const uint32_t nb = (uint32_t)std::min<uint64_t>(nblk(std::max<uint64_t>(1, n), GV_RF_WG), 1024);
     double* part = dalloc<double>(X, (uint64_t)nb * GV_RF_NV);
-    owned.insert(owned.end(), {didx, ok, pos, dS, part});
+    uint32_t* fin = dalloc<uint32_t>(X, 1);  // workgroups of the running step that have finished
+    owned.insert(owned.end(), {didx, ok, pos, dS, part, fin});
     if (n) HIPCHK(hipMemcpyAsync(didx, idx, n * sizeof(int64_t), hipMemcpyHostToDevice, X.st));
     HIPCHK(hipMemcpyAsync(dS, &S0, sizeof(RefState), hipMemcpyHostToDevice, X.st));
+    HIPCHK(hipMemsetAsync(fin, 0, sizeof(uint32_t), X.st));
     const unsigned gv = gs_grid(X, std::max<uint64_t>(1, n));
     // one round: verification at the current pose, then Gauss-Newton steps
-    // on the verified matches; after the last round, verification and sums
-    for (int round = 0; round <= rounds; round++) {
-      k_rf_verify<<<gv, 256, 0, X.st>>>(dS, cols, didx, n, round == 0 ? T20 : T2, ok);
-      if (round == 0) {
-        k_rf_accum<<<nb, GV_RF_WG, 0, X.st>>>(dS, cols, didx, n, ok, part);
-        k_rf_solve<<<1, 64, 0, X.st>>>(dS, part, nb, 0);
-        HIPCHK(hipMemcpyAsync(dS + 1, dS, sizeof(RefState), hipMemcpyDeviceToDevice, X.st));
-      }
-      if (round == rounds) break;
-      for (int it = 0; it < iters; it++) {
-        k_rf_accum<<<nb, GV_RF_WG, 0, X.st>>>(dS, cols, didx, n, ok, part);
-        k_rf_solve<<<1, 64, 0, X.st>>>(dS, part, nb, 1);
-      }
-    }
-    k_rf_accum<<<nb, GV_RF_WG, 0, X.st>>>(dS, cols, didx, n, ok, part);
-    k_rf_solve<<<1, 64, 0, X.st>>>(dS, part, nb, 0);
+    // on the verified matches; after the last round, verification and sums.
+    // The first pass of a round verifies; the first of all also keeps the
+    // leaf centre's sums (dS[1]).
+    auto step = [&](int verify, double T, int update, RefState* snap) {
+      k_rf_step<<<nb, GV_RF_WG, 0, X.st>>>(dS, cols, didx, n, verify, T, ok, part, fin, update, snap);
+    };
+    for (int round = 0; round < rounds; round++)
+      for (int it = 0; it < iters; it++)
+        step(it == 0 ? 1 : 0, round == 0 ? T20 : T2, 1, round == 0 && it == 0 ? dS + 1 : nullptr);
+    // (without steps every round verifies at the leaf centre)
+    const bool moved = rounds > 0 && iters > 0;
+    if (!moved) step(1, T20, 0, dS + 1);
+    if (rounds > 0) step(1, T2, 0, nullptr);
     HIPCHK(hipGetLastError());
-    uint64_t nv = 0;
+    RefState out2[2];
     if (n) {
+      int64_t* dv = dalloc<int64_t>(X, n);
+      owned.push_back(dv);
       excl_scan(X, ok, pos, n);
-      uint32_t last[2] = {0, 0};
-      HIPCHK(hipMemcpyAsync(&last[0], pos + n - 1, 4, hipMemcpyDeviceToHost, X.st));
-      HIPCHK(hipMemcpyAsync(&last[1], ok + n - 1, 4, hipMemcpyDeviceToHost, X.st));
-      host_wait(X);
-      nv = (uint64_t)last[0] + last[1];
-      if (nv) {
-        int64_t* dv = dalloc<int64_t>(X, nv);
-        owned.push_back(dv);
-        k_rf_scatter<<<gv, 256, 0, X.st>>>(didx, n, ok, pos, dv);
-        ver.resize(nv);
-        HIPCHK(hipMemcpyAsync(ver.data(), dv, nv * sizeof(int64_t), hipMemcpyDeviceToHost, X.st));
-      }
+      k_rf_scatter<<<gv, 256, 0, X.st>>>(didx, n, ok, pos, dv);
+      fetch(X, out2, dS, sizeof(out2));
+      ver.resize((size_t)out2[0].cnt);  // the matches in the last sums: the verified ones
+      if (!ver.empty()) fetch(X, ver.data(), dv, ver.size() * sizeof(int64_t));
+    } else {
+      fetch(X, out2, dS, sizeof(out2));
     }
-    HIPCHK(hipMemcpyAsync(&S, dS, sizeof(RefState), hipMemcpyDeviceToHost, X.st));
-    HIPCHK(hipMemcpyAsync(&S0out, dS + 1, sizeof(RefState), hipMemcpyDeviceToHost, X.st));
-    host_wait(X);
+    S = out2[0];
+    S0out = out2[1];
   } catch (DevErr& e) {
     st = e.st;
   }
