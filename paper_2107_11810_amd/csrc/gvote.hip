@@ -887,7 +887,7 @@ void read_tot(Run& X, uint64_t* v, int n, uint64_t seq) {
 // workgroup writes them to the host, about 5 GB/s.
 constexpr size_t kFetchBytes = 64u << 10;
 void fetch(Run& X, void* dst, const void* src, size_t bytes) {
-  if (X.hpin && X.dtot == X.hpin_dev && bytes <= (kStageN + 1) * sizeof(uint64_t)) {
+  if (X.hpin && X.dtot == X.hpin_dev && bytes <= kFetchBytes) {
     const uint64_t seq = next_seq();
     k_fetch<<<1, 256, 0, X.st>>>((const uint32_t*)src, (uint32_t)(bytes / 4), (uint32_t*)(X.hpin_dev + 8), X.hpin_dev,
                                  seq);
@@ -1430,10 +1430,21 @@ void plan_chunks(Run& X, Parent* pa, std::vector<std::pair<uint32_t, uint32_t>>&
   const uint64_t stride = std::max<uint64_t>(1, ((uint64_t)nk + kStageN - 1) / kStageN);
   const uint64_t ns = (nk + stride - 1) / stride;  // samples soff[i*stride], plus soff[nk]
   std::vector<uint64_t> s(ns + 1);
-  uint64_t* d = dalloc<uint64_t>(X, ns + 1);
-  k_gather_u64<<<nblk(ns + 1), 256, 0, X.st>>>(pa->soff, nk, stride, d);
-  fetch(X, s.data(), d, (ns + 1) * sizeof(uint64_t));
-  dfree(X, d);
+  if (X.hpin && X.dtot == X.hpin_dev) {
+    // gathered straight into host-coherent memory by many workgroups, the
+    // sequence number by the next kernel
+    const uint64_t seq = next_seq();
+    k_gather_u64<<<nblk(ns + 1), 256, 0, X.st>>>(pa->soff, nk, stride, X.hpin_dev + 8);
+    k_fetch<<<1, 256, 0, X.st>>>(nullptr, 0, nullptr, X.hpin_dev, seq);
+    HIPCHK(hipGetLastError());
+    wait_seq(X, seq);
+    std::memcpy(s.data(), X.hpin + 8, (ns + 1) * sizeof(uint64_t));
+  } else {
+    uint64_t* d = dalloc<uint64_t>(X, ns + 1);
+    k_gather_u64<<<nblk(ns + 1), 256, 0, X.st>>>(pa->soff, nk, stride, d);
+    fetch(X, s.data(), d, (ns + 1) * sizeof(uint64_t));
+    dfree(X, d);
+  }
   auto at = [&](uint64_t i) { return i >= ns ? s[ns] : s[i]; };  // sample i -> soff[min(i*stride, nk)]
   auto rk = [&](uint64_t i) { return (uint32_t)std::min<uint64_t>(i * stride, nk); };
   const int lc = std::min(pa->level + 1, X.P0.Lstar - 1);
