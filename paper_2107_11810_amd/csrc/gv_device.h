@@ -142,6 +142,21 @@ struct __attribute__((aligned(8))) EntP3p { uint32_t lo, hi; };
 // every multiplicity is 1.
 #define GV_P3U_KMAX 127
 struct __attribute__((aligned(4))) EntP3u { uint32_t v; };
+// The same word cut K1 (9) | K2 (9) << 9 | F (14) << 18: where the heights
+// fit 14 bits it holds the lists of one level more, the level with twice the
+// slopes.
+#define GV_P3V_KMAX 255
+#define GV_P3V_FMAX 8191
+struct __attribute__((aligned(4))) EntP3v { uint32_t v; };
+template <typename E> struct OneWord { static constexpr bool value = false; };
+template <> struct OneWord<EntP3u> {
+  static constexpr bool value = true;
+  static constexpr int KB = 8, KMAX = GV_P3U_KMAX, FMAX = GV_P3_FMAX;
+};
+template <> struct OneWord<EntP3v> {
+  static constexpr bool value = true;
+  static constexpr int KB = 9, KMAX = GV_P3V_KMAX, FMAX = GV_P3V_FMAX;
+};
 template <int FAM> struct PackOf { using T = void; };  // no packed entry
 template <> struct PackOf<FAM_LINE2D> { using T = EntL2p; };
 template <> struct PackOf<FAM_PLANE3D> { using T = EntP3p; };
@@ -323,6 +338,15 @@ template <int FAM> __device__ __host__ inline LinS load_ent(const EntS2p& e) {
   return s;
 }
 
+template <int FAM> __device__ __host__ inline LinS load_ent(const EntP3v& e) {
+  LinS s = lin_zero<FAM>();
+  s.K[0][0] = sext_field(e.v, 0, 9);
+  s.K[0][1] = sext_field(e.v, 9, 9);
+  s.F[0] = sext_field(e.v, 18, 14);
+  s.w = 1;
+  return s;
+}
+
 // register state -> entry; a packed store clears ok when a value does not fit
 template <int FAM, typename E> __device__ __host__ inline E store_ent(const LinS& s, bool& ok);
 template <> __device__ __host__ inline EntL2 store_ent<FAM_LINE2D, EntL2>(const LinS& s, bool&) {
@@ -380,6 +404,14 @@ template <> __device__ __host__ inline EntP3u store_ent<FAM_PLANE3D, EntP3u>(con
        s.w == 1;
   EntP3u e;
   e.v = ((uint32_t)s.K[0][0] & 0xffu) | (((uint32_t)s.K[0][1] & 0xffu) << 8) | ((uint32_t)s.F[0] << 16);
+  return e;
+}
+
+template <> __device__ __host__ inline EntP3v store_ent<FAM_PLANE3D, EntP3v>(const LinS& s, bool& ok) {
+  ok = ok && abs(s.K[0][0]) <= GV_P3V_KMAX && abs(s.K[0][1]) <= GV_P3V_KMAX && abs(s.F[0]) <= GV_P3V_FMAX &&
+       s.w == 1;
+  EntP3v e;
+  e.v = ((uint32_t)s.K[0][0] & 0x1ffu) | (((uint32_t)s.K[0][1] & 0x1ffu) << 9) | ((uint32_t)s.F[0] << 18);
   return e;
 }
 

@@ -330,7 +330,8 @@ __global__ void __launch_bounds__(1024) k_cut(const uint32_t* __restrict__ keepc
 }
 
 // one-word unit-weight PLANE3D entries -> 8-byte entries (before grouping)
-__global__ void k_unit_to_p3(const EntP3u* __restrict__ in, uint64_t n, EntP3p* __restrict__ out) {
+template <typename E>
+__global__ void k_unit_to_p3(const E* __restrict__ in, uint64_t n, EntP3p* __restrict__ out) {
   const uint64_t st = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += st) {
     const LinS s = load_ent<FAM_PLANE3D>(in[i]);
@@ -1064,8 +1065,8 @@ __global__ void __launch_bounds__(256) k_compact_lin(LevelC lv, const CWork<NCH>
   const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
   const uint32_t nwork = *nwork_p;
   if constexpr (FAM == FAM_PLANE3D && NCH == 8 &&
-                (std::is_same<EO, EntP3p>::value || std::is_same<EO, EntP3u>::value)) {
-    constexpr bool UW = std::is_same<EO, EntP3u>::value;  // one-word unit-weight child entries
+                (std::is_same<EO, EntP3p>::value || OneWord<EO>::value)) {
+    constexpr bool UW = OneWord<EO>::value;  // one-word unit-weight child entries
     // Every axis splits; child digit = 4 b1 + 2 b2 + b0 (split axes in axis
     // order, most significant first).  The pass test compares
     // t = 2F + pad + S + b1 K1 + b2 K2 - b0 H against [0, R] (unsigned), and
@@ -1125,9 +1126,11 @@ __global__ void __launch_bounds__(256) k_compact_lin(LevelC lv, const CWork<NCH>
           const uint32_t w = (uint32_t)s.w;
           if constexpr (UW) {
             // a one-word input's K and weight always fit
-            if constexpr (!std::is_same<E, EntP3u>::value)
-              fits = fits && abs(K1c) <= GV_P3U_KMAX && abs(K2c) <= GV_P3U_KMAX && (w == 1u || !V[j]);
-            LO[j] = ((uint32_t)K1c & 0xffu) | (((uint32_t)K2c & 0xffu) << 8);
+            using W = OneWord<EO>;
+            constexpr uint32_t KM = (1u << W::KB) - 1u;
+            if constexpr (!std::is_same<E, EO>::value)
+              fits = fits && abs(K1c) <= W::KMAX && abs(K2c) <= W::KMAX && (w == 1u || !V[j]);
+            LO[j] = ((uint32_t)K1c & KM) | (((uint32_t)K2c & KM) << W::KB);
             WHI[j] = 0u;
           } else {
             if constexpr (!std::is_same<E, EntP3p>::value)
@@ -1152,7 +1155,7 @@ __global__ void __launch_bounds__(256) k_compact_lin(LevelC lv, const CWork<NCH>
               fhi = imax32(fhi, Fc);
               EO e;
               if constexpr (UW) {
-                e.v = LO[j] | ((uint32_t)Fc << 16);
+                e.v = LO[j] | ((uint32_t)Fc << (2 * OneWord<EO>::KB));
               } else {
                 e.lo = LO[j];
                 e.hi = ((uint32_t)Fc & 0xffffu) | WHI[j];
@@ -1166,7 +1169,11 @@ __global__ void __launch_bounds__(256) k_compact_lin(LevelC lv, const CWork<NCH>
         }
       }
     }
-    fits = fits && flo >= -GV_P3_FMAX && fhi <= GV_P3_FMAX;
+    constexpr int32_t FM = [] {
+      if constexpr (UW) return OneWord<EO>::FMAX;
+      else return GV_P3_FMAX;
+    }();
+    fits = fits && flo >= -FM && fhi <= FM;
     if (!fits) atomicOr(ovf, 1);
     return;
   }

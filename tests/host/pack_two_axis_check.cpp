@@ -1,8 +1,10 @@
 // Host-side check of the packed list entries of the families with two
-// dependent axes (RAY3D 12 bytes, SIM2D 16 bytes): every value inside the
-// limits round-trips exactly, one field beyond its limit is flagged.
+// dependent axes (RAY3D 12 bytes, SIM2D 16 bytes) and of the one-word PLANE3D
+// entry cut 9 | 9 | 14 bits: every value inside the limits round-trips
+// exactly, one field beyond its limit is flagged.
 #include "../../paper_2107_11810_amd/csrc/gv_device.h"
 #include <cstdio>
+#include <cstdlib>
 
 static int fails = 0;
 #define CHECK(c)                                              \
@@ -64,6 +66,21 @@ int main() {
   static_assert(sizeof(EntR3p) == 12 && sizeof(EntS2p) == 16, "packed entry sizes");
   check<FAM_RAY3D, EntR3p>(GV_R3_WMAX);
   check<FAM_SIM2D, EntS2p>(0x7fffffff);
+  static_assert(sizeof(EntP3v) == 4, "one word");
+  for (int32_t K1 = -GV_P3V_KMAX - 1; K1 <= GV_P3V_KMAX + 1; K1++)
+    for (int32_t K2 : {0, 1, -1, GV_P3V_KMAX, -GV_P3V_KMAX, GV_P3V_KMAX + 1, -GV_P3V_KMAX - 1})
+      for (int32_t F : {0, 1, -1, 4097, GV_P3V_FMAX, -GV_P3V_FMAX, GV_P3V_FMAX + 1, -GV_P3V_FMAX - 1}) {
+        LinS s = lin_zero<FAM_PLANE3D>();
+        s.K[0][0] = K1;
+        s.K[0][1] = K2;
+        s.F[0] = F;
+        s.w = 1;
+        const bool in = abs(K1) <= GV_P3V_KMAX && abs(K2) <= GV_P3V_KMAX && abs(F) <= GV_P3V_FMAX;
+        bool ok = true;
+        const EntP3v e = store_ent<FAM_PLANE3D, EntP3v>(s, ok);
+        CHECK(ok == in);
+        if (in) CHECK(same<FAM_PLANE3D>(load_ent<FAM_PLANE3D>(e), s));
+      }
   {
     LinS s = lin_zero<FAM_RAY3D>();
     s.w = GV_R3_WMAX + 1;

@@ -49,6 +49,9 @@ PROBLEMS = {
     "plane3d_513": lambda: synth.plane3d(seed=513, n=513, n_in=60, sigma=0.004, eps=(0.04, 0.04, 0.04)),
     "plane3d_4096": lambda: synth.plane3d(seed=4096, n=4096, n_in=400, sigma=0.004, eps=(0.04, 0.04, 0.04)),
     "plane3d_9001": lambda: synth.plane3d(seed=9001, n=9001, n_in=700, sigma=0.003, eps=(0.03, 0.03, 0.03)),
+    # slopes of a few steps beside heights of thousands: one-word lists cut 8 | 8 | 16 bits, else 9 | 9 | 14
+    "plane3d_narrow": lambda: synth.plane3d(seed=77, n=2500, n_in=200, sigma=0.004, lo=(-0.02, -0.02, -2.0),
+                                            hi=(0.02, 0.02, 3.0), eps=(0.003, 0.003, 0.01)),
     "plane3d_small": lambda: synth.config("plane3d_small"),
     "plane3d_tiny": lambda: synth.config("plane3d_tiny"),
     "pose4dof_tiny": lambda: synth.config("pose4dof_tiny"),
