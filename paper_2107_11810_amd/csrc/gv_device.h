@@ -94,15 +94,35 @@ struct __attribute__((aligned(16))) EntS2 { int32_t K00, K01, K10, K11, F0, F1, 
 
 // POSE4DOF entries: quantized parameters, weight, index of the root record.
 struct __attribute__((aligned(16))) EntQ32 { float W1, W2, W3, xi, eta; uint32_t w, ridx, _; };
-// unit-weight POSE4DOF lists below the root: the binary32 values and the
-// root index only (24 bytes; every multiplicity is 1)
-struct __attribute__((aligned(8))) EntQ24 { float W1, W2, W3, xi, eta; uint32_t ridx; };
-static_assert(sizeof(EntQ24) == 24 && offsetof(EntQ24, ridx) == 20 && offsetof(EntQ32, eta) == 16 &&
-                  offsetof(EntQ32, ridx) == 24,
-              "the compaction copies these entries as words");
-template <typename E> __device__ inline uint32_t pose_w(const E& e) { return e.w; }
-template <> __device__ inline uint32_t pose_w<EntQ24>(const EntQ24&) { return 1u; }
 struct __attribute__((aligned(16))) EntQ64 { double W1, W2, W3, xi, eta; uint32_t w, ridx; };
+// Unit-weight pose lists below the root hold indices only: the surfaces do
+// not change there, so the values stay in the root's records (EntQ32, EntQ64
+// at ridx), which the caches hold better than copies of 24 or 48 bytes in
+// every list.  Compaction 0.25 against 0.77 ms (50k matches, binary64; 1.89
+// against 2.48 ms in all), 62 against 122 ms (64 served problems; 211 against
+// 249 ms) and 2.5 against 6.4 ms (pose4dof_1m; 31.1 against 33.5 ms, its
+// records no longer fitting one L2: the count pass reads them 15% slower).
+struct __attribute__((aligned(4))) EntI32 { uint32_t ridx; };
+struct __attribute__((aligned(4))) EntI64 { uint32_t ridx; };
+template <typename E> struct RecOf {
+  using T = E;  // the entry is its own record
+  static constexpr bool idx = false;
+};
+template <> struct RecOf<EntI32> {
+  using T = EntQ32;
+  static constexpr bool idx = true;
+};
+template <> struct RecOf<EntI64> {
+  using T = EntQ64;
+  static constexpr bool idx = true;
+};
+// entry i of a list as a record
+template <typename E>
+__device__ inline typename RecOf<E>::T pose_rec(const E* __restrict__ ents, uint64_t i,
+                                                const typename RecOf<E>::T* __restrict__ rec) {
+  if constexpr (RecOf<E>::idx) return rec[ents[i].ridx];
+  else return ents[i];
+}
 
 // Exact-mode linear entry: the root-quantized binary64 parameters t[q][i]
 // (slope of dependent axis q over parameter axis i) and f[q].

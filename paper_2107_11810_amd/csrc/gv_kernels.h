@@ -760,6 +760,7 @@ template <typename E, bool UNIT, bool ALL>
 __global__ void __launch_bounds__(256, 4) k_count_pose(const ProbC* __restrict__ Ptab, int m, LevelC lv,
                                                     const Cell* __restrict__ cells, const Item* __restrict__ items,
                                                     const uint32_t* __restrict__ nitems_p, const E* __restrict__ ents,
+                                                    const typename RecOf<E>::T* __restrict__ rec,
                                                     const double* __restrict__ m64, uint64_t n_root,
                                                     uint16_t* __restrict__ masks, uint32_t* __restrict__ icnt,
                                                     uint32_t* __restrict__ iw,
@@ -793,9 +794,9 @@ __global__ void __launch_bounds__(256, 4) k_count_pose(const ProbC* __restrict__
       const uint64_t ei = I.off + k;
       uint32_t mask = 0, w = 0;
       if (k < cnt) {
-        const E e = ents[ei];
-        w = pose_w(e);
-        if constexpr (sizeof(E) == sizeof(EntQ64)) {
+        const typename RecOf<E>::T e = pose_rec(ents, ei, rec);
+        w = e.w;
+        if constexpr (std::is_same<typename RecOf<E>::T, EntQ64>::value) {
           mask = pose_mask64<ALL>(P, lv, B, sector, e.W1, e.W2, e.W3, e.xi, e.eta);
         } else {
           mask = pose_mask32<ALL>(P, lv, C, m, Bf, sector, e, m64, n_root, nre);
@@ -1222,9 +1223,9 @@ template <> struct WordVec<uint4> {
   using T = uint32_t __attribute__((ext_vector_type(4)));
   __device__ static T of(const uint4& v) { return T{v.x, v.y, v.z, v.w}; }
 };
-template <> struct WordVec<uint2> {
-  using T = uint32_t __attribute__((ext_vector_type(2)));
-  __device__ static T of(const uint2& v) { return T{v.x, v.y}; }
+template <> struct WordVec<uint32_t> {
+  using T = uint32_t;
+  __device__ static T of(uint32_t v) { return v; }
 };
 
 // Masked families: the stored pass masks say who goes where, and entries are
@@ -1263,12 +1264,11 @@ __global__ void __launch_bounds__(256) k_compact(LevelC lv, const Item* __restri
     // G entries per lane in registers, survivors written child by child:
     // one sequential run per child list instead of one interleaved piece
     // per child and row
-    // Entries move as words the copy never looks inside (16-byte words,
-    // or 8-byte ones for the 24-byte unit entry).  EntQ32 -> EntQ24 drops
-    // the weight (1 in a unit list) and the padding on the way.
-    constexpr bool CONV = std::is_same<E, EntQ32>::value && std::is_same<EO, EntQ24>::value;
-    static_assert(CONV || std::is_same<E, EO>::value, "pose entries are copied whole");
-    using Wd = std::conditional_t<sizeof(EO) % 16 == 0, uint4, uint2>;
+    // Entries move as words the copy never looks inside (16-byte words, or
+    // the 4 bytes of an index).  A root record becomes its index on the way.
+    constexpr bool CONV = RecOf<EO>::idx && !RecOf<E>::idx;
+    static_assert(CONV || std::is_same<E, EO>::value, "masked entries are copied whole");
+    using Wd = std::conditional_t<sizeof(EO) % 16 == 0, uint4, uint32_t>;
     constexpr int NV = sizeof(EO) / sizeof(Wd);
     // (32-child masks: fewer entries per lane, the store loop runs per child)
     constexpr int G = sizeof(EO) <= 32 && NCP <= 16 ? 16 : 8;
@@ -1292,14 +1292,7 @@ __global__ void __launch_bounds__(256) k_compact(LevelC lv, const Item* __restri
       for (int j = 0; j < G; j++) {
         const uint64_t ei = I.off + k0 + 64 * j + lane;
         if constexpr (CONV) {
-          uint4 lo = make_uint4(0u, 0u, 0u, 0u), hi = lo;
-          if (mk[j]) {
-            lo = reinterpret_cast<const uint4*>(ents + ei)[0];  // W1 W2 W3 xi
-            hi = reinterpret_cast<const uint4*>(ents + ei)[1];  // eta w ridx pad
-          }
-          ev[j][0] = make_uint2(lo.x, lo.y);
-          ev[j][1] = make_uint2(lo.z, lo.w);
-          ev[j][2] = make_uint2(hi.x, hi.z);
+          ev[j][0] = mk[j] ? ents[ei].ridx : 0u;
         } else {
 #pragma unroll
           for (int q = 0; q < NV; q++) {

@@ -301,7 +301,7 @@ template <bool ALL, typename E>
 __device__ inline uint32_t pose5_mask_of(const ProbC& P, const LevelC& lv, const Cell& C, int m, const Pose5Level& B,
                                          const float* Bf, const E& e, const double* __restrict__ m64,
                                          uint64_t n_root, uint32_t& nre) {
-  if constexpr (std::is_same<E, EntQ64>::value)
+  if constexpr (std::is_same<E, EntQ64>::value)  // (E: a record)
     return pose5_mask64<ALL>(P, lv, B, (int)C.sector, e.W1, e.W2, e.W3, e.xi, e.eta);
   else
     return pose5_mask32<ALL>(P, lv, C, m, Bf, (int)C.sector, e, m64, n_root, nre);
@@ -315,22 +315,27 @@ __device__ inline uint32_t pose5_mask_of(const ProbC& P, const LevelC& lv, const
 // per child).  Thirty-two scalar ballot accumulators, beside the cell's
 // binary64 child boxes, overflowed the scalar registers.
 static_assert(GV_ITEM / 64 <= 255 && 64 * (GV_ITEM / 64) <= 65535, "per-lane byte counters, 16-bit wave sums");
-// E: EntQ64 (binary64 lists) or EntQ32 / EntQ24 (binary32 filter; m64 holds
-// the binary64 root values for the recheck, n_root their column stride).
+// E: EntQ64 / EntI64 (binary64 lists) or EntQ32 / EntI32 (binary32 filter;
+// m64 holds the binary64 root values for the recheck, n_root their column
+// stride).
 // binary32 lists at 4 waves per SIMD (128 registers, 36 B per lane spilled):
 // 1.94-1.96 against 2.02-2.05 ms of count kernel per pose5dof_20k solve at
 // the 3 waves of its unconstrained 142 registers; binary64 lists keep theirs
 // (capping them spilled 224-448 B per lane and ran slower)
-template <typename E> constexpr int pose5_min_blocks() { return std::is_same<E, EntQ64>::value ? 1 : 4; }
+template <typename E> constexpr int pose5_min_blocks() {
+  return std::is_same<typename RecOf<E>::T, EntQ64>::value ? 1 : 4;
+}
 template <typename E, bool UNIT, bool ALL>
 __global__ void __launch_bounds__(256, pose5_min_blocks<E>()) k_count_pose5(const ProbC* __restrict__ Ptab, int m, LevelC lv,
                                                      const Cell* __restrict__ cells, const Item* __restrict__ items,
                                                      const uint32_t* __restrict__ nitems_p, const E* __restrict__ ents,
+                                                     const typename RecOf<E>::T* __restrict__ rec,
                                                      const double* __restrict__ m64, uint64_t n_root,
                                                      uint32_t* __restrict__ masks, uint32_t* __restrict__ icnt,
                                                      uint32_t* __restrict__ iw,
                                                      unsigned long long* __restrict__ rechecks) {
-  constexpr bool F64 = std::is_same<E, EntQ64>::value;
+  using R = typename RecOf<E>::T;
+  constexpr bool F64 = std::is_same<R, EntQ64>::value;
   const uint32_t nch = ALL ? 32u : 1u << lv.abits;
   const uint32_t lane = lane_id();
   const uint32_t wave = uniform_u32((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
@@ -353,7 +358,7 @@ __global__ void __launch_bounds__(256, pose5_min_blocks<E>()) k_count_pose5(cons
         const uint64_t ei = I.off + k;
         uint32_t mask = 0;
         if (k < cnt) {
-          const E e = ents[ei];
+          const R e = pose_rec(ents, ei, rec);
           mask = pose5_mask_of<ALL>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
           masks[ei] = mask;
         }
@@ -381,8 +386,8 @@ __global__ void __launch_bounds__(256, pose5_min_blocks<E>()) k_count_pose5(cons
         const uint64_t ei = I.off + k;
         uint32_t mask = 0, w = 0;
         if (k < cnt) {
-          const E e = ents[ei];
-          w = pose_w(e);
+          const R e = pose_rec(ents, ei, rec);
+          w = e.w;
           mask = pose5_mask_of<ALL>(P, lv, C, m, B, Bf, e, m64, n_root, nre);
           masks[ei] = mask;
         }

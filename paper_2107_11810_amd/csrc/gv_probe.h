@@ -187,8 +187,8 @@ template <int FAM, typename E> constexpr int probe_min_blocks() {
 template <int FAM, typename E>
 __global__ void __launch_bounds__(256, (probe_min_blocks<FAM, E>())) k_probe_pose(
     const ProbC* __restrict__ Ptab, int m, LevelC lv, LevelC lv2, int B, uint64_t idxmask,
-    const Cell* __restrict__ cells, const E* __restrict__ ents, const typename SubFam<FAM>::M* __restrict__ masks,
-    const double* __restrict__ m64, uint64_t n_root, const uint32_t* __restrict__ order,
+    const Cell* __restrict__ cells, const E* __restrict__ ents, const typename RecOf<E>::T* __restrict__ rec,
+    const typename SubFam<FAM>::M* __restrict__ masks, const double* __restrict__ m64, uint64_t n_root, const uint32_t* __restrict__ order,
     const uint32_t* __restrict__ cnent, uint32_t r0, uint32_t r1, const unsigned long long* __restrict__ best,
     uint32_t* keepc, uint64_t* csize, unsigned long long* __restrict__ tests, unsigned long long* __restrict__ reads,
     unsigned long long* __restrict__ rechecks) {
@@ -235,8 +235,8 @@ __global__ void __launch_bounds__(256, (probe_min_blocks<FAM, E>())) k_probe_pos
         const uint32_t n = min(tail - head, 64u);
         uint32_t mask = 0;
         if (lane < n) {
-          const E e = ents[off + q[(head + lane) & 127u]];
-          mask = F::template mask_as<true, E>(P, lv2, C, m + 1, Bx, Bf, e, m64, n_root, nre);
+          const typename RecOf<E>::T e = pose_rec(ents, off + q[(head + lane) & 127u], rec);
+          mask = F::template mask_as<true, typename RecOf<E>::T>(P, lv2, C, m + 1, Bx, Bf, e, m64, n_root, nre);
         }
         head += n;
         seen += n;
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(256, (probe_min_blocks<FAM, E>())) k_probe_pos
   }
   if (lane == 0 && ntests) {
     atomicAdd(tests, (unsigned long long)ntests);
-    atomicAdd(reads, (unsigned long long)nread * sizeof(E));
+    atomicAdd(reads, (unsigned long long)nread * (RecOf<E>::idx ? sizeof(E) + sizeof(typename RecOf<E>::T) : sizeof(E)));
   }
   const uint32_t re = wave_sum_u32(nre);
   if (lane == 0 && re) atomicAdd(rechecks, (unsigned long long)re);

@@ -90,7 +90,8 @@ struct SubFrame {
 template <int FAM, typename E>
 __global__ void __launch_bounds__(GV_SUB_WG) k_subtree_pose(
     const ProbC* __restrict__ Ptab, int m0, const Cell* __restrict__ cells, uint32_t ncell,
-    const E* __restrict__ ents, const double* __restrict__ m64, uint64_t n_root, unsigned long long* best,
+    const E* __restrict__ ents, const typename RecOf<E>::T* __restrict__ rec, const double* __restrict__ m64,
+    uint64_t n_root, unsigned long long* best,
     unsigned long long* __restrict__ rechecks, unsigned long long* __restrict__ tests,
     uint32_t* __restrict__ next_cell, Cell* __restrict__ over, uint32_t* __restrict__ nover,
     E* __restrict__ fbuf, typename SubFam<FAM>::M* __restrict__ mbuf, int nframes) {
@@ -153,9 +154,9 @@ __global__ void __launch_bounds__(GV_SUB_WG) k_subtree_pose(
           const uint32_t j = base + tid;
           uint32_t mask = 0, w = 0;
           if (j < len) {
-            const E e = list[j];
-            w = pose_w(e);
-            mask = F::template mask<E>(P, lv, C, l, B, Bf, e, m64, n_root, nre);
+            const typename RecOf<E>::T e = pose_rec(list, j, rec);
+            w = e.w;
+            mask = F::template mask<typename RecOf<E>::T>(P, lv, C, l, B, Bf, e, m64, n_root, nre);
             masks[j] = (M)mask;
           }
 #pragma unroll
@@ -163,7 +164,7 @@ __global__ void __launch_bounds__(GV_SUB_WG) k_subtree_pose(
             const bool p = (mask >> ch) & 1u;
             const uint32_t n = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(p));
             uint32_t s = n;  // unit entries: the count is the number of survivors
-            if constexpr (!std::is_same<E, EntQ24>::value) s = wave_sum_u32(p ? w : 0u);
+            if constexpr (!RecOf<E>::idx) s = wave_sum_u32(p ? w : 0u);
             if (lane == 0) {
               wnent[wv][ch] += n;
               wcnt[wv][ch] += s;

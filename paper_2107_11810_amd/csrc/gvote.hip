@@ -650,7 +650,8 @@ struct Run {
   int pack_from = 1 << 30;                // lists of this level and deeper use the packed entry
   int unit_from = 1 << 30;                // PLANE3D unit-weight lists of this level and deeper: one word
   bool unit9 = false;                     // (cut 9 | 9 | 14 bits instead of 8 | 8 | 16)
-  bool q24 = false;                       // POSE4DOF unit-weight lists below the root: 24-byte entries
+  bool qidx = false;                      // pose unit-weight lists below the root hold indices (EntI32, EntI64)
+  void* rec = nullptr;                    // ... of these root records, owned
   size_t ent_bytes = 0;
   uint64_t chunk_bytes = 0;               // device bytes one materialized chunk may need
   uint64_t first_cells = 262144;          // cells in the first chunk of every expansion
@@ -1125,7 +1126,8 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
 
   // work items: at most 2^ilog <= GV_ITEM entries of one cell each (the
   // count pass's surface tile, autotuned on large batches)
-  const uint64_t tbytes = fam_masked(FAM) ? nlive * (sizeof(E) + sizeof(M)) : nlive * sizeof(E);
+  const uint64_t rbytes = RecOf<E>::idx ? sizeof(E) + sizeof(typename RecOf<E>::T) : sizeof(E);  // read per entry
+  const uint64_t tbytes = fam_masked(FAM) ? nlive * (rbytes + sizeof(M)) : nlive * rbytes;
   int tcand;
   uint32_t ilog = tile_pick(X, tbytes, &tcand);
   if constexpr (FAM == FAM_POSE5DOF)
@@ -1163,7 +1165,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
   if constexpr (FAM == FAM_POSE5DOF) {
 #define GV_COUNT_POSE5(U, A)                                                                                     \
   k_count_pose5<E, U, A><<<grid, 256, 0, X.st>>>(X.dP, m, lv, b.cells, pa->items, pa->nitems, (const E*)b.ents,   \
-                                                X.m64, X.Ntot, (uint32_t*)pa->masks, itemcnt, itemw, X.drecheck)
+                                                (const typename RecOf<E>::T*)X.rec, X.m64, X.Ntot, (uint32_t*)pa->masks, itemcnt, itemw, X.drecheck)
     static_assert(std::is_same<M, uint32_t>::value, "5-DoF masks are 32-bit");
     const bool all = lv.abits == 5;
     if (b.unit) {
@@ -1177,7 +1179,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
   } else if constexpr (FAM == FAM_POSE4DOF) {
 #define GV_COUNT_POSE(U, A)                                                                                 \
   k_count_pose<E, U, A><<<grid, 256, 0, X.st>>>(X.dP, m, lv, b.cells, pa->items, pa->nitems, (const E*)b.ents, \
-                                                X.m64, X.Ntot, (uint16_t*)pa->masks, itemcnt, itemw, X.drecheck)
+                                                (const typename RecOf<E>::T*)X.rec, X.m64, X.Ntot, (uint16_t*)pa->masks, itemcnt, itemw, X.drecheck)
     // every axis splits at most levels: that variant has no per-axis checks
     const bool all = lv.abits == 4;
     if (b.unit) {
@@ -1489,7 +1491,7 @@ bool want_probe(const Run& X, const Parent* pa) {
 // families, entries and levels the probe kernels take: every axis splits at
 // the parent's level (linear) and at the children's
 template <int FAM, typename E> constexpr bool probe_family() {
-  return FAM == FAM_PLANE3D ? sizeof(E) <= 8 : fam_pose(FAM) && !std::is_same<E, EntQ32>::value;
+  return FAM == FAM_PLANE3D ? sizeof(E) <= 8 : fam_pose(FAM) && RecOf<E>::idx;
 }
 template <int FAM, typename E> bool probe_fits(const ProbC& P, int level) {
   if (!probe_family<FAM, E>() || level + 1 >= P.Lstar) return false;
@@ -1506,8 +1508,8 @@ void probe_chunk(Run& X, Parent* pa, uint32_t r0, uint32_t r1, uint32_t* keepc, 
                                                         keepc, csize, X.dtests, X.dtests + 1);
   } else if constexpr (probe_family<FAM, E>()) {
     k_probe_pose<FAM, E><<<nblk(r1 - r0, 4), 256, 0, X.st>>>(
-        X.dP, pa->level, lv, lv2, P.B, P.idxmask, pa->cells, (const E*)pa->ents, (const M*)pa->masks, X.m64, X.Ntot,
-        pa->order, pa->cnent, r0, r1, X.dbest, keepc, csize, X.dtests, X.dtests + 1, X.drecheck);
+        X.dP, pa->level, lv, lv2, P.B, P.idxmask, pa->cells, (const E*)pa->ents,
+        (const typename RecOf<E>::T*)X.rec, (const M*)pa->masks, X.m64, X.Ntot, pa->order, pa->cnent, r0, r1, X.dbest, keepc, csize, X.dtests, X.dtests + 1, X.drecheck);
   }
 }
 
@@ -1633,7 +1635,7 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
   dfree(X, csize);
   if (!fresh) dfree(X, coff);
   if (--pa->pending == 0) free_parent(X, pa);
-  if constexpr (std::is_same<EO, EntQ24>::value) {
+  if constexpr (RecOf<EO>::idx) {
     // used only where no list is grouped
     if (made && want_group(X, nb)) throw DevErr{GV_EINVAL};
   } else if constexpr (OneWord<EO>::value) {
@@ -1653,6 +1655,9 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
   return made;
 }
 
+// the index entry of a pose root record
+template <typename E> using IndexT = std::conditional_t<std::is_same<E, EntQ64>::value, EntI64, EntI32>;
+
 // Entry type of a level's lists: the packed entry from pack_from on.
 template <int FAM, typename E>
 using PackedT = std::conditional_t<fam_pose(FAM) || std::is_void_v<typename PackOf<FAM>::T>, E,
@@ -1664,8 +1669,8 @@ Parent* expand_at(Run& X, Batch& b, bool own_ents, bool dive, bool lend = false)
     if (b.unit && b.level >= X.unit_from)
       return X.unit9 ? expand<FAM, EntP3v, M>(X, b, own_ents, dive, lend)
                      : expand<FAM, EntP3u, M>(X, b, own_ents, dive, lend);
-  if constexpr ((FAM == FAM_POSE4DOF || FAM == FAM_POSE5DOF) && std::is_same<E, EntQ32>::value)
-    if (b.unit && b.level >= 1 && X.q24) return expand<FAM, EntQ24, M>(X, b, own_ents, dive, lend);
+  if constexpr (fam_pose(FAM))
+    if (b.unit && b.level >= 1 && X.qidx) return expand<FAM, IndexT<E>, M>(X, b, own_ents, dive, lend);
   if (b.level >= X.pack_from) return expand<FAM, PackedT<FAM, E>, M>(X, b, own_ents, dive, lend);
   return expand<FAM, E, M>(X, b, own_ents, dive, lend);
 }
@@ -1681,10 +1686,10 @@ bool materialize_word(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
 template <int FAM, typename E, typename M>
 bool materialize_at(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
   using EP = PackedT<FAM, E>;
-  if constexpr ((FAM == FAM_POSE4DOF || FAM == FAM_POSE5DOF) && std::is_same<E, EntQ32>::value) {
-    if (pa->unit && X.q24) {
-      if (pa->level >= 1) return materialize<FAM, EntQ24, EntQ24, M>(X, pa, r0, r1, nb);
-      return materialize<FAM, EntQ32, EntQ24, M>(X, pa, r0, r1, nb);
+  if constexpr (fam_pose(FAM)) {
+    if (pa->unit && X.qidx) {
+      if (pa->level >= 1) return materialize<FAM, IndexT<E>, IndexT<E>, M>(X, pa, r0, r1, nb);
+      return materialize<FAM, E, IndexT<E>, M>(X, pa, r0, r1, nb);
     }
   }
   if constexpr (FAM == FAM_PLANE3D) {
@@ -1936,7 +1941,9 @@ void start_search(Run& X) {
         HIPCHK(hipMemcpyAsync(ents + cells[i].off, (E*)X.root + src.off, (size_t)src.len * sizeof(E),
                               hipMemcpyDeviceToDevice, X.st));
     }
-    dfree(X, X.root);
+    // (unmerged root records stay: a list's indices are places in them)
+    if (unit && X.qidx) X.rec = X.root;
+    else dfree(X, X.root);
   }
   X.root = nullptr;
   auto upload_cells = [&]() {
@@ -2054,8 +2061,8 @@ void run_subtree(Run& X, Batch& b) {
   Cell* over = dalloc<Cell>(X, b.ncell);
   uint32_t* ctr = dalloc<uint32_t>(X, 3);
   HIPCHK(hipMemsetAsync(ctr, 0, 3 * sizeof(uint32_t), X.st));
-  k_subtree_pose<FAM, E><<<G, GV_SUB_WG, 0, X.st>>>(X.dP, b.level, b.cells, b.ncell, (const E*)b.ents, X.m64,
-                                                     X.Ntot, X.dbest, X.drecheck, X.dtests, ctr, over, ctr + 1, fbuf,
+  k_subtree_pose<FAM, E><<<G, GV_SUB_WG, 0, X.st>>>(X.dP, b.level, b.cells, b.ncell, (const E*)b.ents,
+                                                     (const typename RecOf<E>::T*)X.rec, X.m64, X.Ntot, X.dbest, X.drecheck, X.dtests, ctr, over, ctr + 1, fbuf,
                                                      mbuf, nframes);
   HIPCHK(hipGetLastError());
   uint32_t back[2] = {0, 0};
@@ -2089,11 +2096,9 @@ bool subtree_at(Run& X, Batch& b) {
   } else {
     if (!X.subtree || X.report || b.level < X.subtree_from || b.level + 1 >= X.P0.Lstar) return false;
     free_counts(X);  // (the device search counts this batch itself)
-    if constexpr (std::is_same<E, EntQ32>::value) {
-      if (b.unit && b.level >= 1 && X.q24) {
-        run_subtree<FAM, EntQ24>(X, b);
-        return true;
-      }
+    if (b.unit && b.level >= 1 && X.qidx) {
+      run_subtree<FAM, IndexT<E>>(X, b);
+      return true;
     }
     run_subtree<FAM, E>(X, b);
     return true;
@@ -2336,7 +2341,7 @@ bool build_pose(Run& X) {
     if (pr->st == GV_OK && !pr->filter_ok) all32 = false;
   }
   // (grouping below the root is off for this family unless forced)
-  X.q24 = X.ctx->pack && X.group_mode <= 0;
+  X.qidx = X.ctx->pack && X.group_mode <= 0;
   if (X.fam == GV_POSE5DOF) {
     if (all32) {
       dfree(X, e64);
@@ -2505,6 +2510,8 @@ void epoch_release(Run& X) {
   free_counts(X);
   dfree(X, X.root);
   X.root = nullptr;
+  dfree(X, X.rec);
+  X.rec = nullptr;
   dfree(X, X.m64);
   X.m64 = nullptr;
   for (ProbRec* pr : X.probs) {
