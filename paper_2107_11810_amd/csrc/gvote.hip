@@ -2010,6 +2010,7 @@ void start_search(Run& X) {
         have_reuse = true;
         keep = true;
       }
+      if (dv && b.level == 0) carried = false;  // (greedy from the root: later batches miss cells)
       Parent* pa = expand_at<FAM, E, M>(X, b, keep ? false : own, dv, keep);
       if (!pa) break;
       uint32_t r1 = pa->nkept;
