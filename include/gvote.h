@@ -166,8 +166,8 @@ typedef struct {
   uint32_t levels;            /* L*: depth of the leaves */
   double ms_total, ms_kernels;
   /* with kernel_timing: summed event time, launches and algorithmic bytes
-   * of the incidence-test kernel (entries read; the pose families also write a pass
-   * mask per entry) and of the compaction kernel (entries of the parents
+   * of the incidence-test kernels (entries read; the pose families also write a pass
+   * mask per entry; the look-ahead's reads of the parents' lists included) and of the compaction kernel (entries of the parents
    * with a child in the chunk read, pose masks read, children written) */
   double test_ms, compact_ms;
   uint64_t test_launches, compact_launches;

@@ -3,8 +3,9 @@
 // Work decomposition: a batch holds cells of one level, each with a
 // contiguous list of canonical surfaces.  Lists are cut into items of at most
 // 2^ilog <= GV_ITEM entries (the batch's item size) that belong to a single
-// cell; one wavefront processes one item, so the cell's child boxes are wave-uniform (scalar registers) and the
-// per-child counts reduce across the wave before a single atomic per child.
+// cell; one wavefront processes one item, so the cell's child
+// boxes are wave-uniform (scalar registers) and the item's per-child counts
+// are written as one row, summed per cell by k_cell_scan.
 #pragma once
 #include "gv_device.h"
 
