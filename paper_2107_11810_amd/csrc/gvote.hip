@@ -1891,6 +1891,7 @@ void start_search(Run& X) {
   const int nsec = P.nsec;
   std::vector<Cell>& rc = X.root_lists;
   rc.clear();
+  uint64_t live = 0;  // entries of the problems still valid
   for (uint32_t p = 0; p < np; p++) {
     if (X.probs[p]->st != GV_OK) continue;
     Cell c{};
@@ -1898,14 +1899,31 @@ void start_search(Run& X) {
     c.len = (uint32_t)X.probs[p]->n;
     c.prob = p;
     rc.push_back(c);
+    live += c.len;
   }
   if (rc.empty()) return;
+  // A problem that failed in its root kernels leaves its part of the entries
+  // unwritten: then the others' lists are put back to back first, so that
+  // below every entry belongs to a list and the lists start at 0.
+  if (live != X.Ntot) {
+    E* packed = dalloc<E>(X, live);
+    uint64_t at = 0;
+    for (Cell& c : rc) {
+      if (c.len)
+        HIPCHK(hipMemcpyAsync(packed + at, (E*)X.root + c.off, (size_t)c.len * sizeof(E), hipMemcpyDeviceToDevice,
+                              X.st));
+      c.off = at;
+      at += c.len;
+    }
+    X.rec = X.root;  // (indices are places in the whole array)
+    X.root = packed;
+  }
   bool unit = true;
   {
     Batch rb;
     rb.level = 0;
     rb.ncell = (uint32_t)rc.size();
-    rb.nent = X.Ntot;
+    rb.nent = live;
     rb.cells = dalloc<Cell>(X, rc.size());
     if (X.group_mode >= 0) {
       HIPCHK(hipMemcpyAsync(rb.cells, rc.data(), rc.size() * sizeof(Cell), hipMemcpyHostToDevice, X.st));
@@ -1942,7 +1960,7 @@ void start_search(Run& X) {
                               hipMemcpyDeviceToDevice, X.st));
     }
     // (unmerged root records stay: a list's indices are places in them)
-    if (unit && X.qidx) X.rec = X.root;
+    if (unit && X.qidx && !X.rec) X.rec = X.root;
     else dfree(X, X.root);
   }
   X.root = nullptr;
