@@ -2244,6 +2244,10 @@ void build_linear(Run& X) {
       X.pack_from = m;
     }
   }
+  // (tests: pack from this level on whatever the bound says; a value that does
+  // not fit is the device's range check's to report)
+  if (const char* e = std::getenv("GV_PACK_FROM"))
+    if (X.ctx->pack && nmax <= wmax) X.pack_from = std::max(1, atoi(e));
   // PLANE3D: first level from which unit-weight lists fit one word, in the
   // cut of its fields that reaches further up.  The level whose slopes take 9
   // bits holds most of the entries that the probes leave: its lists in 4
@@ -2385,6 +2389,17 @@ bool build_pose(Run& X) {
   return all32;
 }
 
+// A packed list entry that could not hold its value (`ovf`: the device's flag)
+// fails every problem of the epoch.
+void check_packed(Run& X, uint64_t ovf) {
+  if (!ovf) return;
+  for (ProbRec* pr : X.probs)
+    if (pr->st == GV_OK) {
+      pr->st = GV_ERANGE;
+      pr->err = "internal: a lattice value outgrew its packed list entry";
+    }
+}
+
 // per-problem winner, replay, inliers, point; releases the epoch's memory
 void epoch_finish(Run& X) {
   const uint32_t np = (uint32_t)X.probs.size();
@@ -2397,14 +2412,7 @@ void epoch_finish(Run& X) {
   std::memcpy(best.data(), h.data(), np * 8);
   unsigned long long ctr[5];
   std::memcpy(ctr, h.data() + lead, sizeof(ctr));
-  int ovf = 0;
-  std::memcpy(&ovf, &ctr[4], sizeof(int));
-  if (ovf)
-    for (ProbRec* pr : X.probs)
-      if (pr->st == GV_OK) {
-        pr->st = GV_ERANGE;
-        pr->err = "internal: a lattice value outgrew its packed list entry";
-      }
+  check_packed(X, ctr[4]);
   // columns and paths of every problem, uploaded in one copy
   std::vector<char> tab(np * (sizeof(Cols) + sizeof(PathC)));
   bool all_ok = true;
@@ -2980,7 +2988,10 @@ gv_status gv_report(gv_ctx* ctx, const gv_problem* p, uint64_t tau, uint64_t* le
       }
       const uint64_t nn = d2h1(X, X.rep_n);
       total = nn;
-      X.stats.tests += d2h1(X, X.dtests);
+      unsigned long long ctr[5];  // as in epoch_finish
+      fetch(X, ctr, X.dtests, sizeof(ctr));
+      X.stats.tests += ctr[0];
+      check_packed(X, ctr[4]);
       const uint64_t k = std::min<uint64_t>(nn, cap);
       if (k > 0) {
         std::vector<uint64_t> hi(k);
