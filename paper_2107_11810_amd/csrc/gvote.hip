@@ -2427,13 +2427,13 @@ void epoch_finish(Run& X) {
     all_ok = all_ok && pr->st == GV_OK;
     tot += pr->count;
   }
-  char* dtab = dalloc<char>(X, tab.size());
-  const Cols* dctab = (const Cols*)dtab;
-  const PathC* dpaths = (const PathC*)(dtab + np * sizeof(Cols));
-  HIPCHK(hipMemcpyAsync(dtab, tab.data(), tab.size(), hipMemcpyHostToDevice, X.st));
   std::vector<uint32_t> bnd(np + 1, 0);
   std::vector<int64_t> all;
   if (X.Ntot > 0) {
+    char* dtab = dalloc<char>(X, tab.size());
+    const Cols* dctab = (const Cols*)dtab;
+    const PathC* dpaths = (const PathC*)(dtab + np * sizeof(Cols));
+    HIPCHK(hipMemcpyAsync(dtab, tab.data(), tab.size(), hipMemcpyHostToDevice, X.st));
     uint32_t* flag = dalloc<uint32_t>(X, X.Ntot);
     uint32_t* pos = dalloc<uint32_t>(X, X.Ntot + 1);
     int* dbad = X.dbad;  // (faulty observations were reported when the roots were built)
@@ -2466,7 +2466,7 @@ void epoch_finish(Run& X) {
     }
     tot = std::min<uint64_t>(tot, X.Ntot);
     int64_t* dout = dalloc<int64_t>(X, tot);
-    k_write_inliers<<<gg, 256, 0, X.st>>>(flag, pos, X.dooff, np, X.Ntot, tot, dout);
+    if (tot) k_write_inliers<<<gg, 256, 0, X.st>>>(flag, pos, X.dooff, np, X.Ntot, tot, dout);
     HIPCHK(hipGetLastError());
     all.resize(tot);
     if (tot * sizeof(int64_t) <= kFetchBytes) {
@@ -2476,13 +2476,14 @@ void epoch_finish(Run& X) {
       host_wait(X);
     }
     if (all_ok) fetch(X, bnd.data(), dbnd, (np + 1) * sizeof(uint32_t));
+    dfree(X, dtab);
     dfree(X, dbnd);
     dfree(X, dout);
     dfree(X, flag);
     dfree(X, pos);
   }
   if (!X.ev.empty()) host_wait(X);
-  X.idle = true;
+  X.idle = true;  // (a wait follows the last launch on every path above)
   // kernel timing
   for (auto& e : X.ev) {
     float ms = 0.f;
@@ -2518,7 +2519,6 @@ void epoch_finish(Run& X) {
     }
     pr->inliers.assign(all.begin() + (int64_t)bnd[p], all.begin() + (int64_t)bnd[p + 1]);
   }
-  dfree(X, dtab);
 }
 
 // free everything an epoch may still hold (also after an error)
