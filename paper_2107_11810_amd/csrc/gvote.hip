@@ -2017,7 +2017,8 @@ void start_search(Run& X) {
     bool own = false;
     bool carried = X.reuse && !X.root_dive && !X.fixed;
     while (true) {
-      const bool dv = b.ncell >= X.dive_cells;
+      // (greedy to the end once it is: X.counts belongs to the main search)
+      const bool dv = have_reuse || b.ncell >= X.dive_cells;
       bool keep = false;
       if (dv && carried && !have_reuse && b.level > 0) {
         // the greedy expansion below keeps this batch's entries (not owned)
