@@ -197,6 +197,12 @@ __device__ __host__ inline EntP3p pack_p3(int32_t K1, int32_t K2, int32_t F, uin
 // floor(x/2), bit 1 of x, is odd (an even x loses the added 1 in the shift)
 __device__ __host__ inline int32_t rne_half(int32_t x) { return (x + ((x >> 1) & 1)) >> 1; }
 
+// Whether x + shift lies in [0, R].  The sum wraps (unsigned: a signed one
+// must not), so the shift GV_NOWHERE puts every |x| < 2^30 outside any
+// R < 2^30, the limits of the integer tests.
+#define GV_NOWHERE 0x80000000u
+__device__ __host__ constexpr bool in_range(int32_t x, uint32_t shift, uint32_t R) { return (uint32_t)x + shift <= R; }
+
 __device__ inline int32_t imin32(int32_t a, int32_t b) { return a < b ? a : b; }
 __device__ inline int32_t imax32(int32_t a, int32_t b) { return a < b ? b : a; }
 

@@ -88,8 +88,8 @@ __global__ void __launch_bounds__(256) k_probe_p3(LevelC lv, LevelC lv2, int B, 
       nread += min(len - k0, 64u * G);
       // X = 2F, SP = pad + S, and in the child SB = pad' + S', RR = R'.
       // Lanes past the list's end get an SP that passes nothing.
-      int32_t X[G], KA[G], KB[G], SP[G], KA1[G], KB1[G], SB[G];
-      uint32_t R[G], RR[G];
+      int32_t X[G], KA[G], KB[G], KA1[G], KB1[G], SB[G];
+      uint32_t SP[G], R[G], RR[G];
 #pragma unroll
       for (int j = 0; j < G; j++) {
         const LinS s = load_ent<FAM_PLANE3D>(ev[j]);
@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(256) k_probe_p3(LevelC lv, LevelC lv2, int B, 
         X[j] = 2 * s.F[0];
         KA[j] = s.K[0][0];
         KB[j] = s.K[0][1];
-        SP[j] = k0 + 64 * j + lane < len ? pad + S : (int32_t)0x80000000;
+        SP[j] = k0 + 64 * j + lane < len ? (uint32_t)(pad + S) : GV_NOWHERE;
         R[j] = (uint32_t)(2 * S + (H + 2 * pad) - (KA[j] + KB[j]));
         KA1[j] = rne_half(KA[j]);
         KB1[j] = rne_half(KB[j]);
@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(256) k_probe_p3(LevelC lv, LevelC lv2, int B, 
     uint32_t got = 0, n[8] = {0, 0, 0, 0, 0, 0, 0, 0};                                                                 \
     _Pragma("unroll") for (int j = 0; j < G; j++) {                                                                    \
       const int32_t x = X[j] + ((I & 4) ? KA[j] : 0) + ((I & 2) ? KB[j] : 0) - ((I & 1) ? H : 0);                      \
-      const bool p = (uint32_t)(x + SP[j]) <= R[j];                                                                    \
+      const bool p = in_range(x, SP[j], R[j]);                                                                         \
       got += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(p));                                                       \
       /* 2 rne(x / 2) + pad' + S'; out of every grandchild's range where the child's own test fails */                 \
       const int32_t U = p ? ((x + ((x >> 1) & 1)) & ~1) + SB[j] : (int32_t)0x40000000;                                 \
