@@ -249,6 +249,20 @@ __global__ void __launch_bounds__(1024) k_front(LevelC lv, int B, uint64_t idxma
   }
 }
 
+// the first n kept children's arrays (n + 1 offsets) into others
+__global__ void k_copy_kept(const uint32_t* __restrict__ order, const uint32_t* __restrict__ scount,
+                            const uint64_t* __restrict__ soff, uint32_t n, uint32_t* __restrict__ order_out,
+                            uint32_t* __restrict__ scount_out, uint64_t* __restrict__ soff_out) {
+  const uint64_t st = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += st) {
+    soff_out[i] = soff[i];
+    if (i < n) {
+      order_out[i] = order[i];
+      scount_out[i] = scount[i];
+    }
+  }
+}
+
 // Greedy dive above the leaves: every cell keeps its best child (count, then
 // lowest digit), in parent order, so rank r is cell r.
 template <bool WRITE>

@@ -1256,6 +1256,26 @@ bool one_chunk(const Run& X, const Parent* pa) {
          (double)pa->kept_entries * per_ent + (double)pa->nkept * per_cell <= (double)X.chunk_bytes;
 }
 
+// The pruning writes the kept children's order, counts and offsets before
+// their number is known, into room for every child (16 bytes each).  While
+// they wait for their chunks they keep room for themselves alone, as soon as
+// that gives back a mebibyte (below it, a launch costs more than the room).
+constexpr uint64_t kRoomSlack = 65536;
+void shrink_kept(Run& X, Parent* pa) {
+  const uint32_t n = pa->nkept;
+  uint32_t* order = dalloc<uint32_t>(X, n);
+  uint32_t* scount = dalloc<uint32_t>(X, n);
+  uint64_t* soff = dalloc<uint64_t>(X, n + 1ull);
+  k_copy_kept<<<gs_grid(X, n + 1ull), 256, 0, X.st>>>(pa->order, pa->scount, pa->soff, n, order, scount, soff);
+  HIPCHK(hipGetLastError());
+  dfree(X, pa->order);
+  dfree(X, pa->scount);
+  dfree(X, pa->soff);
+  pa->order = order;
+  pa->scount = scount;
+  pa->soff = soff;
+}
+
 // Puts a parent's kept children in descending count order (several problems
 // in a batch: of the count relative to their problem's largest).
 void sort_kept(Run& X, Parent* pa, const uint32_t* ccnt, uint32_t nch) {
@@ -1264,6 +1284,8 @@ void sort_kept(Run& X, Parent* pa, const uint32_t* ccnt, uint32_t nch) {
   uint32_t* key = pa->scount;
   uint32_t* pmax = nullptr;
   pa->sorted = true;
+  dfree(X, pa->soff);  // (the parent order's: made again below)
+  pa->soff = nullptr;
   pa->order = dalloc<uint32_t>(X, nkept);
   if (X.probs.size() > 1) {
     pmax = dalloc<uint32_t>(X, X.probs.size());
@@ -1298,6 +1320,7 @@ void sort_kept(Run& X, Parent* pa, const uint32_t* ccnt, uint32_t nch) {
   }
   dfree(X, kid);
   uint32_t* sn = dalloc<uint32_t>(X, nkept);
+  pa->soff = dalloc<uint64_t>(X, nkept + 1ull);
   k_rank<<<nblk(nkept), 256, 0, X.st>>>(pa->order, nkept, pa->cnent, ccnt, pa->rank_of, sn, pa->scount);
   if (nkept <= GV_SMALL_N) {
     k_scan_small<uint32_t, uint64_t><<<1, 1024, 0, X.st>>>(sn, pa->soff, nkept, pa->soff + nkept);
@@ -1402,10 +1425,16 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
   pa->kept_entries = kt[1];
   pa->best = kt[2];
   X.stats.cells_pruned += nk - kt[0];
+  uint64_t room = nsel;
+  if (pa->nkept && nsel - pa->nkept > kRoomSlack) {
+    shrink_kept(X, pa);
+    room = pa->nkept;
+  }
   if (X.trace) {
     const uint64_t bst = d2h1(X, X.dbest);
-    std::fprintf(stderr, "gv: level %d cells %u entries %llu kept %u best %llu%s%s\n", m, b.ncell,
-                 (unsigned long long)b.nent, pa->nkept, (unsigned long long)(bst >> P.B), dive ? " (dive)" : "",
+    std::fprintf(stderr, "gv: level %d cells %u entries %llu kept %u (room %llu of %llu) best %llu%s%s\n", m, b.ncell,
+                 (unsigned long long)b.nent, pa->nkept, (unsigned long long)room, (unsigned long long)nk,
+                 (unsigned long long)(bst >> P.B), dive ? " (dive)" : "",
                  (b.unit && m >= X.unit_from) ? " one-word" : (m >= X.pack_from ? " packed" : ""));
   }
   if (pa->nkept == 0) {
