@@ -770,6 +770,11 @@ void dfree(Run& X, void* p) {
   if (p) X.cache->put(p);
 }
 
+// between the two launches of a bookkeeping kernel of g workgroups
+void part_scan(Run& X, FSum* part, unsigned g) {
+  if (g > GV_PART_DIRECT) k_part_scan<<<1, 1024, 0, X.st>>>(part, g);
+}
+
 template <typename In, typename Out>
 void excl_scan(Run& X, const In* in, Out* out, uint64_t n) {
   if (n == 0) return;
@@ -1144,6 +1149,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
     const unsigned g = nblk(b.ncell, GV_FRONT_WG);
     FSum* part = dalloc<FSum>(X, g);
     k_items<1, false><<<g, GV_FRONT_WG, 0, X.st>>>(b.cells, b.ncell, ilog, part, pa->ioff, pa->items, pa->nitems);
+    part_scan(X, part, g);
     k_items<1, true><<<g, GV_FRONT_WG, 0, X.st>>>(b.cells, b.ncell, ilog, part, pa->ioff, pa->items, pa->nitems);
     dfree(X, part);
   }
@@ -1402,14 +1408,20 @@ Parent* expand(Run& X, Batch& b, bool own_ents, bool dive, bool lend) {
 #define GV_PICK(W)                                                                                              \
   k_pick<W><<<g, wg, 0, X.st>>>(lv, b.ncell, ccnt, pa->cnent, part, pa->order, pa->scount, pa->rank_of, pa->soff, \
                                   X.dtot, seq)
-    if (g > 1) GV_PICK(false);
+    if (g > 1) {
+      GV_PICK(false);
+      part_scan(X, part, g);
+    }
     GV_PICK(true);
 #undef GV_PICK
   } else {
 #define GV_FRONT(W)                                                                                              \
   k_front<W><<<g, wg, 0, X.st>>>(lv, P.B, P.idxmask, b.cells, nk, ccnt, pa->cnent, X.dbest, part, pa->order,     \
                                    pa->scount, pa->rank_of, pa->soff, X.dtot, seq)
-    if (g > 1) GV_FRONT(false);
+    if (g > 1) {
+      GV_FRONT(false);
+      part_scan(X, part, g);
+    }
     GV_FRONT(true);
 #undef GV_FRONT
   }
@@ -1583,7 +1595,10 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
 #define GV_CUT(W)                                                                                               \
   k_cut<W><<<g, wg, 0, X.st>>>(keepc, csize, nr, part, cidx, coff, pa->order, r0, lv.abits, pa->ioff, pa->ncell, \
                                  pa->nitems, pa->sorted ? 1 : 0, linear ? 1 : 0, X.dtot, seq)
-    if (g > 1) GV_CUT(false);
+    if (g > 1) {
+      GV_CUT(false);
+      part_scan(X, part, g);
+    }
     GV_CUT(true);
 #undef GV_CUT
     HIPCHK(hipGetLastError());
