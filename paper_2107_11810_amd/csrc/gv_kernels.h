@@ -583,7 +583,8 @@ __device__ inline void put_row(const uint32_t (&an)[NC], const uint32_t (&aw)[NC
 // zeroed counters, one atomic per item and child, and a device-wide scan over
 // every (child, item) (pose5dof_20k 2.96 against 3.21 ms, 64 served problems
 // 266 against 290 ms).
-// A cell of length len owns ceil(len / 2^ilog) items from ioff[cell].
+// A cell of length len owns ceil(len / 2^ilog) items from ioff[cell]; one
+// thread takes a (cell, child), a serial chain of an eighth of them.
 template <int NCH, bool UNIT>
 __global__ void k_cell_scan(const Cell* __restrict__ cells, uint32_t ncell, uint32_t ilog, const uint32_t* __restrict__ ioff,
                             const uint32_t* __restrict__ icnt, const uint32_t* __restrict__ iw,
@@ -593,8 +594,7 @@ __global__ void k_cell_scan(const Cell* __restrict__ cells, uint32_t ncell, uint
   const uint32_t c = (uint32_t)(t / NCH), ch = (uint32_t)(t % NCH);
   const uint32_t i0 = ioff[c], ni = items_of(cells[c].len, ilog);
   uint64_t n = 0, w = 0;
-  // eight items' loads at once: a cell of the upper levels owns up to a
-  // thousand items, one thread each child
+  // eight items' loads at once
   for (uint32_t i = 0; i < ni; i += 8) {
     const uint64_t k = (uint64_t)(i0 + i) * NCH + ch;
     uint32_t v[8], u[8];
@@ -610,6 +610,45 @@ __global__ void k_cell_scan(const Cell* __restrict__ cells, uint32_t ncell, uint
       if constexpr (!UNIT) w += u[j];
     }
   }
+  cnent[t] = (uint32_t)n;
+  ccnt[t] = (uint32_t)(UNIT ? n : w);
+}
+
+// The same for a few long cells: one wave per (cell, child), lanes over the
+// items.  Four cells of 977 items and 16 children 11.6 against 68 us, of 20
+// thousand items 191 against 1584.  Up to 32 items a cell both take 6 us, and
+// many cells lose (4096 of 32 items 22.2 against 8.9 us): taken for at most
+// GV_SCAN_WAVES waves and from a mean of GV_SCAN_ITEMS items on.
+#define GV_SCAN_WAVES 1024u
+#define GV_SCAN_ITEMS 32u
+template <int NCH, bool UNIT>
+__global__ void __launch_bounds__(256) k_cell_scan_long(const Cell* __restrict__ cells, uint32_t ncell, uint32_t ilog,
+                                                        const uint32_t* __restrict__ ioff,
+                                                        const uint32_t* __restrict__ icnt,
+                                                        const uint32_t* __restrict__ iw,
+                                                        uint64_t* __restrict__ itemoff, uint32_t* __restrict__ ccnt,
+                                                        uint32_t* __restrict__ cnent) {
+  const uint32_t lane = lane_id();
+  const uint64_t t = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (t >= (uint64_t)ncell * NCH) return;  // (whole waves)
+  const uint32_t c = (uint32_t)(t / NCH), ch = (uint32_t)(t % NCH);
+  const uint32_t i0 = ioff[c], ni = items_of(cells[c].len, ilog);
+  uint64_t n = 0, w = 0;
+  for (uint32_t i = 0; i < ni; i += 64) {
+    const bool in = i + lane < ni;
+    const uint64_t k = (uint64_t)(i0 + i + lane) * NCH + ch;
+    const uint32_t v = in ? icnt[k] : 0u;
+    uint32_t x = v;  // (64 items' entries, and their weights, fit 32 bits)
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if (lane >= (uint32_t)o) x += y;
+    }
+    if (itemoff && in) itemoff[k] = n + (x - v);
+    n += __shfl(x, 63, 64);
+    if constexpr (!UNIT) w += wave_sum_u32(in ? iw[k] : 0u);
+  }
+  if (lane != 0) return;
   cnent[t] = (uint32_t)n;
   ccnt[t] = (uint32_t)(UNIT ? n : w);
 }

@@ -1229,9 +1229,14 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
   HIPCHK(hipGetLastError());
   // per-cell counts and per-item offsets from the items' rows
   if (!leaf) pa->itemoff = dalloc<uint64_t>(X, (uint64_t)nch * pa->max_items);
+  const bool wide = nk <= GV_SCAN_WAVES && (nlive >> ilog) >= (uint64_t)GV_SCAN_ITEMS * b.ncell;
 #define GV_CELL_SCAN(U, N)                                                                                      \
-  k_cell_scan<N, U><<<nblk((uint64_t)b.ncell * N), 256, 0, X.st>>>(b.cells, b.ncell, ilog, pa->ioff, itemcnt, \
-                                                                   itemw, pa->itemoff, ccnt, pa->cnent)
+  if (wide)                                                                                                     \
+    k_cell_scan_long<N, U><<<nblk(nk, 4), 256, 0, X.st>>>(b.cells, b.ncell, ilog, pa->ioff, itemcnt, itemw,     \
+                                                          pa->itemoff, ccnt, pa->cnent);                        \
+  else                                                                                                          \
+    k_cell_scan<N, U><<<nblk(nk), 256, 0, X.st>>>(b.cells, b.ncell, ilog, pa->ioff, itemcnt, itemw, pa->itemoff, \
+                                                  ccnt, pa->cnent)
   switch ((b.unit ? 64 : 0) | nch) {
     case 64 | 2: GV_CELL_SCAN(true, 2); break;
     case 64 | 4: GV_CELL_SCAN(true, 4); break;
