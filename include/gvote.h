@@ -218,7 +218,12 @@ gv_status gv_destroy(gv_ctx *ctx);
  * canonization and grouping, a dive that seeds the best key, depth-first
  * frontier expansion with pruning, best-key reduction, path-replay inlier
  * extraction) on the context's stream.  gv_solve calls on one context are
- * serialized; they may run while submitted problems are served. */
+ * serialized; they may run while submitted problems are served.
+ * The search reads small totals from the device many times; the calling
+ * thread (a serving lane's for submitted problems) polls for each up to 200
+ * microseconds, busy on its core, before it waits for the stream.  The
+ * environment variable GV_POLL_US, read by gv_create, sets that time: 0 on a
+ * host with fewer cores than threads that solve. */
 gv_status gv_solve(gv_ctx *ctx, const gv_problem *p, gv_result *r);
 
 /* Threshold reporting (the ray-intersection setting of Sec. 4.3: every cell

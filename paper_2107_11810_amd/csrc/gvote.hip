@@ -280,6 +280,7 @@ struct gv_ctx {
   std::mutex tmu;
   gvi_tune_slot tune[kLastFam + 1][kTuneKinds];
   bool autotune = true;
+  int poll_us = 200;                  // how long a host wait polls before it waits for the stream (GV_POLL_US)
   uint64_t tune_min = kTuneMinBytes;  // launches of fewer entry bytes are not tuning samples
   std::string tune_path;   // autotune cache file ("" = keep choices in memory)
   std::string arch;        // device architecture name, the cache file's key
@@ -855,13 +856,14 @@ uint64_t next_seq() {
 // Waits until a kernel has put `seq` into the host-coherent totals block.
 // Polled first (seen a few microseconds after it is written; a stream wait
 // adds a barrier packet and its cache release), then, for a kernel that runs
-// longer or never writes, the stream wait.  With one upload and polled
+// longer or never writes, the stream wait.  The polling takes the calling
+// thread's core, a serving lane's too; GV_POLL_US=0 leaves it out.  With one upload and polled
 // tables in place of the copies around a solve: line2d_10k 0.71 against
 // 1.11 ms, ray3d_100k 1.23 against 1.61 ms, pose5dof_20k 2.27 against 2.73 ms.
 void wait_seq(Run& X, uint64_t seq) {
   const volatile uint64_t* f = X.hpin + GV_TOT_SEQ;
   const auto t0 = std::chrono::steady_clock::now();
-  for (;;) {
+  while (X.ctx->poll_us > 0) {
     for (int i = 0; i < 32; i++) {
       if (*f == seq) {
         std::atomic_thread_fence(std::memory_order_acquire);
@@ -871,7 +873,7 @@ void wait_seq(Run& X, uint64_t seq) {
       }
       __builtin_ia32_pause();
     }
-    if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) break;
+    if (std::chrono::steady_clock::now() - t0 >= std::chrono::microseconds(X.ctx->poll_us)) break;
   }
   host_wait(X);
 }
@@ -2942,6 +2944,7 @@ gv_status gv_create(gv_ctx** out, const gv_ctx_config* cfg) {
   if (const char* e = std::getenv("GV_MAX_BATCH")) c->max_batch = (size_t)std::max(1, atoi(e));
   if (const char* e = std::getenv("GV_BATCH_N")) c->batch_n = std::strtoull(e, nullptr, 10);
   if (const char* e = std::getenv("GV_PACK")) c->pack = atoi(e) != 0;
+  if (const char* e = std::getenv("GV_POLL_US")) c->poll_us = std::max(0, atoi(e));
   *out = c;
   return GV_OK;
 }
