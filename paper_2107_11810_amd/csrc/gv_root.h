@@ -31,7 +31,7 @@ __device__ inline uint32_t prob_of(const uint64_t* __restrict__ ooff, uint32_t n
   return lo;
 }
 
-__global__ void k_front(int fam, const ProbC* __restrict__ Pp, Cols cols, int64_t n, double* __restrict__ t,
+__global__ void k_front_end(int fam, const ProbC* __restrict__ Pp, Cols cols, int64_t n, double* __restrict__ t,
                         double* __restrict__ f, int32_t* __restrict__ tag, int* __restrict__ bad) {
   const ProbC& P = *Pp;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {

@@ -3398,7 +3398,7 @@ gv_status gv_parametrize(gv_ctx* ctx, const gv_problem* p, double* t_out, double
       int32_t* tg = dalloc<int32_t>(X, p->n);
       int* bad = dalloc<int>(X, 1);
       HIPCHK(hipMemsetAsync(bad, 0, sizeof(int), X.st));
-      k_front<<<gs_grid(X, p->n), 256, 0, X.st>>>((int)p->family, X.dP, cols, p->n, t, f, tg, bad);
+      k_front_end<<<gs_grid(X, p->n), 256, 0, X.st>>>((int)p->family, X.dP, cols, p->n, t, f, tg, bad);
       HIPCHK(hipMemcpyAsync(t_out, t, p->n * 4 * sizeof(double), hipMemcpyDeviceToHost, X.st));
       HIPCHK(hipMemcpyAsync(f_out, f, p->n * 2 * sizeof(double), hipMemcpyDeviceToHost, X.st));
       if (tag_out) HIPCHK(hipMemcpyAsync(tag_out, tg, p->n * sizeof(int32_t), hipMemcpyDeviceToHost, X.st));
