@@ -1115,6 +1115,9 @@ bool want_group(const Run& X, const Batch& b) {
   return avg >= 0.5 * X.lat_bound[b.level];
 }
 
+// entries without a weight (indices, one-word): every multiplicity is 1
+template <typename E> constexpr bool unit_only() { return RecOf<E>::idx || OneWord<E>::value; }
+
 // The count pass of one batch: its work items, the incidence test of every
 // (surface, child) pair, and the per-child counts (ccnt) and entries and each
 // item's offsets in the child lists.  The masked families also leave their
@@ -1128,6 +1131,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
   const bool leaf = (m + 1 == P.Lstar);
   const uint64_t nk = (uint64_t)b.ncell * nch;
   const uint64_t nlive = std::min(b.nent, b.nlive);
+  if (unit_only<E>() && !b.unit) throw DevErr{GV_EINVAL};
   X.stats.tests += nlive * nch;
   X.stats.cells_expanded += b.ncell;
 
@@ -1179,7 +1183,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
     if (b.unit) {
       if (all) GV_COUNT_POSE5(true, true);
       else GV_COUNT_POSE5(true, false);
-    } else {
+    } else if constexpr (!unit_only<E>()) {
       if (all) GV_COUNT_POSE5(false, true);
       else GV_COUNT_POSE5(false, false);
     }
@@ -1193,7 +1197,7 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
     if (b.unit) {
       if (all) GV_COUNT_POSE(true, true);
       else GV_COUNT_POSE(true, false);
-    } else {
+    } else if constexpr (!unit_only<E>()) {
       if (all) GV_COUNT_POSE(false, true);
       else GV_COUNT_POSE(false, false);
     }
@@ -1206,8 +1210,11 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
       k_count_x<fam_base(FAM), false, M><<<grid, 256, 0, X.st>>>(X.dP, m, lv, b.cells, pa->items, pa->nitems,
                                                              (const EntX*)b.ents, (M*)pa->masks, itemcnt, itemw);
   } else {
-#define GV_COUNT_LIN(U, N) \
-  k_count_lin<FAM, U, E, N><<<grid, 256, 0, X.st>>>(lv, pa->items, pa->nitems, (const E*)b.ents, itemcnt, itemw)
+#define GV_COUNT_LIN(U, N)                                                                                       \
+  do {                                                                                                           \
+    if constexpr ((U) || !unit_only<E>())                                                                        \
+      k_count_lin<FAM, U, E, N><<<grid, 256, 0, X.st>>>(lv, pa->items, pa->nitems, (const E*)b.ents, itemcnt, itemw); \
+  } while (0)
     switch ((b.unit ? 32 : 0) | nch) {
       case 32 | 2: GV_COUNT_LIN(true, 2); break;
       case 32 | 4: GV_COUNT_LIN(true, 4); break;
