@@ -1553,6 +1553,13 @@ template <int FAM, typename E> bool probe_fits(const ProbC& P, int level) {
   return P.lev[level + 1].abits == P.d && (fam_pose(FAM) || P.lev[level].abits == P.d);
 }
 
+// (trace) the entries a probe reads
+template <int FAM, typename E> const char* probe_name() {
+  if (RecOf<E>::idx) return std::is_same<E, EntI64>::value ? "EntI64" : "EntI32";
+  if (std::is_same<E, EntP3v>::value) return "EntP3v";
+  return OneWord<E>::value ? "EntP3u" : "EntP3p";
+}
+
 template <int FAM, typename E, typename M>
 void probe_chunk(Run& X, Parent* pa, uint32_t r0, uint32_t r1, uint32_t* keepc, uint64_t* csize) {
   const ProbC& P = X.P0;
@@ -1619,6 +1626,10 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
     dfree(X, part);
     read_tot(X, tot, linear ? 4 : 2, seq);
   }
+  if (X.trace && !fresh)
+    std::fprintf(stderr, "gv: level %d chunk %u-%u of %u%s%s%s: %llu left\n", pa->level, r0, r1, pa->nkept,
+                 pa->sorted ? " by count" : "", probe ? " probed " : "", probe ? probe_name<FAM, E>() : "",
+                 (unsigned long long)tot[0]);
   bool made = false;
   X.stats.cells_pruned += nr - tot[0];
   if (tot[0] > 0) {

@@ -1,4 +1,4 @@
-"""Frontiers of more workgroups than add up each other's sums (over 2048 of
+"""Chunks at the edges of one workgroup, and frontiers of more workgroups than add up each other's sums (over 2048 of
 256 threads): cells' items, pruned children, greedy picks and re-cut chunks
 with their prefixes scanned between the launches.  Results equal the oracle's
 (whole numbers)."""
@@ -13,6 +13,7 @@ from paper_2107_11810_amd import synth
 
 pytestmark = pytest.mark.gpu
 
+CHUNK = re.compile(r"gv: level \d+ chunk (\d+)-(\d+) of \d+")
 TRACE = re.compile(r"gv: level \d+ cells (\d+) entries \d+ kept (\d+) \(room \d+ of (\d+)\)")
 
 
@@ -64,3 +65,21 @@ def test_greedy_dive_of_a_large_frontier(ctx, monkeypatch, capfd):
     assert max(int(m) for m in re.findall(r"cells (\d+) entries \d+ kept .*\(dive\)", err)) > 2048 * 256  # k_pick
     assert (r["count"], r["leaf_index"]) == (ro["count"], ro["leaf_index"])
     assert np.array_equal(r["inliers"], ro["inliers"])
+
+
+# around one and four elements a thread of a 1024-thread workgroup
+@pytest.mark.parametrize("cells", [1023, 1024, 1025, 4095, 4096, 4097])
+def test_chunks_at_the_edges_of_a_workgroup(ctx, monkeypatch, capfd, cells):
+    g = synth.line2d(seed=6, n=600, n_in=60)
+    P = oracle.Problem(g["family"], g["cols"], g["lo"], g["hi"], g["eps"])
+    tau = oracle.solve(P)["count"] // 8
+    io, co = oracle.report(P, tau)
+    monkeypatch.setenv("GV_FIRST_CELLS", str(cells))
+    monkeypatch.setenv("GV_TRACE", "1")
+    print("chunk edges", cells, flush=True)
+    sys.stdout.flush()
+    capfd.readouterr()
+    ig, cg, _ = ctx.report(g["family"], g["cols"], g["lo"], g["hi"], g["eps"], tau)
+    sizes = [int(m[2]) - int(m[1]) for m in CHUNK.finditer(capfd.readouterr().err)]
+    assert cells in sizes
+    assert np.array_equal(ig, io) and np.array_equal(cg, co)
