@@ -55,9 +55,9 @@ VALU_LANE_OPS = 256 * 64 * 2.4e9
 WORKLOADS = {
     "plane3d_1m": dict(desc="3D plane fitting by point-plane duality: n=1e6 points in the unit cube, 1% inliers "
                             "on a random plane with vertical noise 0.001, eps 0.003 on (a1, a2, a0)",
-                       kernel="k_count_lin<PLANE3D>", compact="k_compact_lin<PLANE3D>", bound="hbm"),
+                       kernel="k_probe_p3 + k_count_lin<PLANE3D>", compact="k_compact_lin<PLANE3D>", bound="alu"),
     "pose4dof_1m": dict(desc="gravity-aligned 4-DoF pose: 1e6 matches in a 200 m box, 0.5% inliers with 0.5 deg "
-                             "bearing noise, eps 0.5 m / 0.5 deg", kernel="k_count_pose<POSE4DOF>",
+                             "bearing noise, eps 0.5 m / 0.5 deg", kernel="k_probe_pose + k_count_pose<POSE4DOF>",
                         compact="k_compact<POSE4DOF>", bound="alu"),
     "pose5dof_20k": dict(desc="gravity-aligned pose with unknown focal length (x, y, z, yaw, f): 2e4 matches, 1.5% "
                               "inliers with 0.5 deg bearing noise, camera within 50 m / 5 m of the truth, f within "
@@ -323,6 +323,12 @@ POSE_DAG_OPS_PER_TEST = 497.0 / 16.0
 # above plus 9 per (z bit, f bit) and 27 per (kappa bit, f bit); child
 # masks 32.  827 operations for 32 tests.
 POSE5_DAG_OPS_PER_TEST = 827.0 / 32.0
+# The same count for the plane predicate (8 children): the slopes' positive
+# parts and their sum S 3; u = 2 F + pad + S 3; the range 2 S - K1 - K2 + (H +
+# 2 pad) 4; u under the other slope bits 3; per slope bits u - H and two
+# comparisons (4 x 3).  25 operations for 8 tests.
+PLANE3D_OPS_PER_TEST = 25.0 / 8.0
+OPS_PER_TEST = {"plane3d": PLANE3D_OPS_PER_TEST, "pose4dof": POSE_DAG_OPS_PER_TEST, "pose5dof": POSE5_DAG_OPS_PER_TEST}
 
 
 def cpu_model():
@@ -403,17 +409,18 @@ def single_leg(name, args, ctx, warmup, steps):
             "bytes_per_launch": int(kb / kn) if kn else None,
             "kernel_ms_per_step": round(kms / len(results), 2),
             "other_kernel_ms_per_step": round((c_ms if kname == W["kernel"] else t_ms) / len(results), 2),
-            # both big kernels: the incidence test (count pass) and compaction
+            # the incidence tests (count pass and, where it runs, the
+            # look-ahead, timed together) and the compaction
             "kernels": [per_kernel(W["kernel"], t_ms, t_b, t_n, len(results)),
                         per_kernel(W["compact"], c_ms, c_b, c_n, len(results))]}
     if c_ms > 0 and c_wb:
-        # the same two kernels counted with each entry read once per expansion
-        # (by the count pass) and written once (by the compaction): the
+        # the same kernels counted with each entry read once per expansion (by
+        # the test kernels) and written once (by the compaction): the
         # compaction's re-read of its parents is left out of its work
         roof["kernels"][1]["write_achieved"] = round(c_wb / (c_ms * 1e-3) / 1e9, 1)
         roof["kernels"][1]["write_frac"] = round(c_wb / (c_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)
         pb = (t_b + c_wb) / (t_ms + c_ms) / 1e6 if t_ms + c_ms > 0 else 0.0
-        roof["path"] = {"basis": "count-pass reads plus compaction child writes, over both kernels' time",
+        roof["path"] = {"basis": "test-kernel reads plus compaction child writes, over their time",
                         "bytes_per_step": int((t_b + c_wb) / len(results)),
                         "ms_per_step": round((t_ms + c_ms) / len(results), 2),
                         "achieved": round(pb, 1), "unit": "GB/s", "frac": round(pb / HBM_PEAK_GBS, 4)}
@@ -426,11 +433,11 @@ def single_leg(name, args, ctx, warmup, steps):
         # operations per test of the predicate's definition, times the tests,
         # over its event time; beside it the measured issue rate (VALU
         # instructions x 64 lanes per test, from the counter record)
-        opt = POSE5_DAG_OPS_PER_TEST if g["family"] == "pose5dof" else POSE_DAG_OPS_PER_TEST
+        opt = OPS_PER_TEST[g["family"]]
         ach = opt * tests / (kms * 1e-3) / 1e12
         roof.update({"bound": "alu", "achieved": round(ach, 2), "peak": VALU_LANE_OPS / 1e12,
                      "unit": "T ops/s", "frac": round(ach / (VALU_LANE_OPS / 1e12), 4),
-                     "ops_per_test": round(opt, 2), "traffic": None})
+                     "ops_per_test": round(opt, 2)})
         issued = measured_valu(name, kname)
         if issued is not None:
             roof["issued_lane_ops_per_test"] = round(issued, 2)

@@ -331,7 +331,7 @@ __global__ void __launch_bounds__(1024) k_pick(LevelC lv, uint32_t ncell, const 
 
 // Offsets of a re-cut chunk of nr children (keepc, csize as k_chunk_keep and
 // the probe leave them): each one's cell index and list offset, and the
-// totals tot[0], tot[1] (kept cells, their entries).  With nwork (linear
+// totals tot[0], tot[1] (kept cells, their entries).  With `linear` (linear
 // families), tot[2], tot[3] = the items the chunk [r0, r0 + nr) can draw from:
 // in parent order (sorted == 0) its children belong to a contiguous range of
 // parent cells, in count order to any.
@@ -424,8 +424,9 @@ __device__ inline void axis_pass(const int32_t* K, int32_t F, int32_t H, int32_t
 // entries that came with it: sim2d_90k count 1.4 against 5.7 ms and
 // compaction 2.3 against 5.5 ms per solve (5.5 against 12.4 ms in all),
 // ray3d_100k count 0.19 against 0.61 and compaction 0.29 against 0.95 ms (2.0
-// against 3.1 ms).  Bound now by the list bytes (2.3-2.7 TB/s over launches
-// of all sizes).
+// against 3.1 ms).  sim2d_90k by counters: the count moves 3.7 TB/s (0.7 of the
+// card's copy rate) at 52% of the vector issue rate, the compaction 3.1 TB/s
+// (0.6) at 49%: list bytes and vector work bound them together.
 // PLANE3D with all three axes splitting (digit = b_a1 b_a2 b_a0): with
 // c = max(K, 0), child (b1, b2, b0) is met iff
 //   0 <= u - b0 H <= H + 2 pad + |K1| + |K2|,  u = 2F + pad + c1 + c2 + b1 K1 + b2 K2,
@@ -1085,8 +1086,9 @@ __global__ void k_emit_ranked(LevelC lv, const Cell* __restrict__ cells, const u
 // Compaction of one chunk: survivors whose child's rank lies in [r0, r1) go
 // into that child's list, canonized to it.  Write positions are known in
 // advance: the count pass recorded every item's per-child survivors, and
-// their exclusive scan (itemoff, child-major) gives each item's offset inside
-// the child's list; within an item, a wavefront ballot ranks the lanes.
+// their prefixes within the cell (itemoff, a row of children per item) give
+// each item's offset inside the child's list; within an item, a wavefront
+// ballot ranks the lanes.
 // ---------------------------------------------------------------------------
 // Work list of one linear-family compaction pass: the items whose cell has a
 // child in the chunk, each with its kept children and, per kept child, where

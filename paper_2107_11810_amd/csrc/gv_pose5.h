@@ -318,7 +318,7 @@ static_assert(GV_ITEM / 64 <= 255 && 64 * (GV_ITEM / 64) <= 65535, "per-lane byt
 // E: EntQ64 / EntI64 (binary64 lists) or EntQ32 / EntI32 (binary32 filter;
 // m64 holds the binary64 root values for the recheck, n_root their column
 // stride).
-// binary32 lists at 4 waves per SIMD (128 registers, 36 B per lane spilled):
+// binary32 lists at 4 waves per SIMD (128 registers, 44 B per lane spilled):
 // 1.94-1.96 against 2.02-2.05 ms of count kernel per pose5dof_20k solve at
 // the 3 waves of its unconstrained 142 registers; binary64 lists keep theirs
 // (capping them spilled 224-448 B per lane and ran slower)

@@ -713,12 +713,10 @@ struct Run {
   std::chrono::steady_clock::time_point t0;
 };
 
-// Two host-coherent pinned words that kernels write totals to, so the host
-// reads them after a stream wait without a copy.  Null pointers (and device
-// memory plus a copy) when the allocation fails.
-// Layout: 8 words of totals (the last one a sequence number), then
-// kStageN + 1 words that the chunk planner's samples and small device tables
-// are copied into.
+// Host-coherent pinned memory that kernels write to and the host polls: 8
+// words of totals (the last one a sequence number), then kStageN + 1 words
+// that the chunk planner's samples and small device tables are copied into.
+// Null pointers (and device memory plus a copy) when the allocation fails.
 constexpr uint64_t kStageN = 65536;
 void alloc_hpin(uint64_t*& h, uint64_t*& d) {
   h = d = nullptr;
@@ -1267,6 +1265,8 @@ void count_pass(Run& X, Batch& b, Parent* pa, uint32_t*& ccnt) {
 
 // Whether every kept child fits the first chunk the schedule would cut (the
 // same rule as plan_chunks, decided from the totals already on the host).
+// Entries are counted at the root's size: lists of indices and packed entries
+// need less than is planned for them.
 bool one_chunk(const Run& X, const Parent* pa) {
   const int lc = std::min(pa->level + 1, X.P0.Lstar - 1);
   const double per_cell = 64.0 + 40.0 * (double)(1u << X.P0.lev[lc].abits);
@@ -2151,8 +2151,8 @@ void run_subtree(Run& X, Batch& b) {
   uint32_t* ctr = dalloc<uint32_t>(X, 3);
   HIPCHK(hipMemsetAsync(ctr, 0, 3 * sizeof(uint32_t), X.st));
   k_subtree_pose<FAM, E><<<G, GV_SUB_WG, 0, X.st>>>(X.dP, b.level, b.cells, b.ncell, (const E*)b.ents,
-                                                     (const typename RecOf<E>::T*)X.rec, X.m64, X.Ntot, X.dbest, X.drecheck, X.dtests, ctr, over, ctr + 1, fbuf,
-                                                     mbuf, nframes);
+                                                     (const typename RecOf<E>::T*)X.rec, X.m64, X.Ntot, X.dbest,
+                                                     X.drecheck, X.dtests, ctr, over, ctr + 1, fbuf, mbuf, nframes);
   HIPCHK(hipGetLastError());
   uint32_t back[2] = {0, 0};
   fetch(X, back, ctr + 1, 2 * sizeof(uint32_t));
