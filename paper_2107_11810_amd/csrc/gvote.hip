@@ -1532,12 +1532,26 @@ void plan_chunks(Run& X, Parent* pa, std::vector<std::pair<uint32_t, uint32_t>>&
 // pose5dof_20k (children of 300 entries) took 3.54 against 3.24 ms and 64
 // served problems (10 to 400) 841 against 294 ms.  Under kProbeMin entries in
 // all, the launch and the wait for the totals cost what the lists would.
+// A wave walks its list alone (a parent cell's; pose: a child's), so a chunk
+// of few of them, as small memory cuts it, leaves the chip idle for the time
+// of the longest list: 14 cells of 16 thousand entries 216 us, their
+// compaction 14.  So a chunk has a wave for every SIMD: 120 thousand planes,
+// allocation-free, 488 against 973 ms probed all the same and 507 unprobed;
+// 300 thousand in 4 GiB 456 against 689 and 445.  Twice or four times the
+// waves measure the same there and lose in 16 GiB (13.5 and 14.7 against 12.7
+// ms); with the default memory nothing changes.
 constexpr uint64_t kProbeMin = 2ull << 20;
 constexpr double kProbeLen = 1024.0;  // mean entries of a child
-bool want_probe(const Run& X, const Parent* pa) {
+constexpr double kProbeWaves = 4.0;   // waves per compute unit
+// waves that probe a chunk of nr children (parent order: its share of the cells)
+template <int FAM> double probe_waves(const Parent* pa, uint32_t nr) {
+  if (fam_pose(FAM)) return (double)nr;
+  return pa->sorted ? (double)std::min(pa->ncell, nr) : (double)pa->ncell * ((double)nr / (double)pa->nkept);
+}
+template <int FAM> bool want_probe(const Run& X, const Parent* pa, uint32_t nr) {
   if (!X.probe || !pa->unit || X.probs.size() != 1 || !pa->nlive) return false;
   if (X.probe == 2) return true;
-  if (pa->kept_entries < kProbeMin) return false;
+  if (pa->kept_entries < kProbeMin || probe_waves<FAM>(pa, nr) < kProbeWaves * X.ctx->n_cu) return false;
   const double child = (double)pa->kept_entries / (double)pa->nkept;
   const double ratio = child / ((double)pa->nlive / (double)pa->ncell);
   return child >= kProbeLen && ratio * child < (double)(pa->best >> X.P0.B);
@@ -1587,7 +1601,7 @@ bool materialize(Run& X, Parent* pa, uint32_t r0, uint32_t r1, Batch& nb) {
   // pruning: no bound has moved since, so nothing is re-cut (keepc = null) and
   // its sizes are the parent's totals (no wait for the device).  A probe drops
   // children, so such a chunk counts what is left.
-  const bool probe = probe_fits<FAM, E>(P, pa->level) && want_probe(X, pa);
+  const bool probe = probe_fits<FAM, E>(P, pa->level) && want_probe<FAM>(X, pa, nr);
   const bool fresh = pa->fresh && r0 == 0 && r1 == pa->nkept && !probe;
   pa->fresh = false;
   const bool linear = !fam_masked(FAM);
