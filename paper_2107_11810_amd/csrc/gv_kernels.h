@@ -424,8 +424,8 @@ __device__ inline void axis_pass(const int32_t* K, int32_t F, int32_t H, int32_t
 // entries that came with it: sim2d_90k count 1.4 against 5.7 ms and
 // compaction 2.3 against 5.5 ms per solve (5.5 against 12.4 ms in all),
 // ray3d_100k count 0.19 against 0.61 and compaction 0.29 against 0.95 ms (2.0
-// against 3.1 ms).  sim2d_90k by counters: the count moves 3.9 TB/s (0.8 of the
-// card's copy rate) at 60% of the vector issue rate, the compaction 3.0 TB/s
+// against 3.1 ms).  sim2d_90k by counters: the count moves 3.8 TB/s (0.8 of the
+// card's copy rate) at 60% of the vector issue rate, the compaction 3.1 TB/s
 // (0.6) at 48%: list bytes and vector work bound them together.
 // PLANE3D with all three axes splitting (digit = b_a1 b_a2 b_a0): with
 // c = max(K, 0), child (b1, b2, b0) is met iff
